@@ -50,7 +50,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}   # MI355X dense MFMA
+# MI355X dense MFMA; a binary32 product is three binary16 ones on the matrix cores (conv_mfma.hip), so binary32 work is
+# priced at a third of the 16-bit rate (the binary32 instruction's own peak is 157.3)
+PEAK_TFLOPS = {"f32": 2500.0 / 3, "bf16": 2500.0}
 PEAK_HBM_GBS = 8000.0
 
 WORKLOAD_TEXT = {

@@ -14,6 +14,7 @@
 // workspace, in the channels-last fragment layout [F][h][w][C] (fragment index
 // linearised row-major over (row fragment, column fragment)).
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -75,16 +76,35 @@ static ConvImpl choose_impl(int cin, int cout, int fh, int fw, dss_dtype dt) {
     // LDS-staged direct kernel streams them faster; with bfloat16 inputs the
     // MFMA tile still wins)
     if (cin < 16 || (cout <= 8 && dt == DSS_F32)) return CONV_DIRECT;
-    if (dt == DSS_F32 && cin % 4 == 0 && mfma_supports(false, fh, fw)) return CONV_MFMA_F32;
-    if (dt == DSS_BF16 && cin % 8 == 0 && mfma_supports(true, fh, fw)) return CONV_MFMA_BF16;
+    if (dt == DSS_F32 && cin % 4 == 0 && mfma_supports(fh, fw)) return CONV_MFMA_F32;
+    if (dt == DSS_BF16 && cin % 8 == 0 && mfma_supports(fh, fw)) return CONV_MFMA_BF16;
     return CONV_DIRECT;
 }
 
-// Packs one convolution (weights [cout][cin][fh][fw] binary32, cross-correlation
-// order; bias [cout] or NULL) into the layout of the kernel chosen for it and
-// copies it to the current device.
-static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const float* weight, const float* bias_in,
-                              dss_dtype dtype, PlanConv& pc) {
+// The power of two that takes the weights' largest finite magnitude into
+// [2^14, 2^15), within 2^-100 .. 2^100 (1 if there is none), and whether some
+// weight is an infinity or NaN.
+static float weight_scale(const float* w, size_t n, bool* nonfinite) {
+    uint32_t top = 0, any = 0;
+    for (size_t i = 0; i < n; ++i) {
+        uint32_t u;
+        std::memcpy(&u, w + i, 4);
+        u &= 0x7fffffffu;
+        any |= (uint32_t)(u >= 0x7f800000u);
+        top = std::max(top, u >= 0x7f800000u ? 0u : u);
+    }
+    *nonfinite = any != 0;
+    if (top == 0) return 1.f;
+    return std::ldexp(1.f, std::max(-100, std::min(100, 14 - ((int)(top >> 23) - 127))));
+}
+
+// Packs one convolution for the kernel chosen for it and copies it to the current
+// device: out channel n, in channel c, tap t has weight host[n sn + c sc + t], or
+// with flip host[n sn + c sc + taps - 1 - t]; `dev` is the same array on the
+// device (the MFMA layouts are packed there, on the null stream).  scale and
+// nonfinite are weight_scale()'s (binary32).  bias [cout] on the host or NULL.
+static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const float* host, const WeightView& dev,
+                              float scale, const float* bias_in, dss_dtype dtype, PlanConv& pc) {
     pc.cin = cin;
     pc.cout = cout;
     pc.fh = fh;
@@ -92,67 +112,39 @@ static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const 
     pc.act = act;
     pc.impl = choose_impl(cin, cout, fh, fw, dtype);
     const bool bf16 = dtype == DSS_BF16;
-    std::vector<float> bias;
-    std::vector<char> wbuf;
-    size_t wbytes = 0;
+    std::vector<float> wbuf;
+    hipError_t e = hipSuccess;
     if (pc.impl == CONV_DIRECT) {
         // [fh][fw][cin][cout_pad] binary32 (bfloat16-rounded values for bfloat16 plans)
         pc.cob = cout >= 16 ? 16 : cout >= 8 ? 8 : cout >= 4 ? 4 : cout >= 2 ? 2 : 1;
         pc.cout_pad = (cout + pc.cob - 1) / pc.cob * pc.cob;
-        wbytes = sizeof(float) * (size_t)fh * fw * cin * pc.cout_pad;
-        wbuf.assign(wbytes, 0);
-        float* w = reinterpret_cast<float*>(wbuf.data());
+        const int taps = fh * fw;
+        wbuf.assign((size_t)taps * cin * pc.cout_pad, 0.f);
         for (int o = 0; o < cout; ++o)
             for (int i = 0; i < cin; ++i)
-                for (int th = 0; th < fh; ++th)
-                    for (int tw = 0; tw < fw; ++tw) {
-                        float v = weight[(((size_t)o * cin + i) * fh + th) * fw + tw];
-                        if (bf16) {
-                            const uint32_t u = (uint32_t)host_f32_to_bf16(v) << 16;
-                            std::memcpy(&v, &u, 4);
-                        }
-                        w[(((size_t)th * fw + tw) * cin + i) * pc.cout_pad + o] = v;
+                for (int t = 0; t < taps; ++t) {
+                    float v = host[o * dev.sn + i * dev.sc + (dev.flip ? taps - 1 - t : t)];
+                    if (bf16) {
+                        const uint32_t u = (uint32_t)host_f32_to_bf16(v) << 16;
+                        std::memcpy(&v, &u, 4);
                     }
-    } else if (pc.impl == CONV_MFMA_F32) {
-        pc.bn = mfma_f32_pick_bn(cout);
-        pc.cin_pad = (cin + 15) / 16 * 16;
-        pc.cout_pad = (cout + pc.bn - 1) / pc.bn * pc.bn;
-        wbytes = sizeof(float) * mfma_f32_packed_floats(pc);
-        wbuf.assign(wbytes, 0);
-        mfma_f32_pack(pc, weight, reinterpret_cast<float*>(wbuf.data()));
+                    wbuf[((size_t)t * cin + i) * pc.cout_pad + o] = v;
+                }
+        const size_t wbytes = sizeof(float) * wbuf.size();
+        e = hipMalloc(&pc.w, wbytes);
+        if (e == hipSuccess) e = hipMemcpy(pc.w, wbuf.data(), wbytes, hipMemcpyHostToDevice);
     } else {
-        pc.bn = mfma_bf16_pick_bn(cout);
+        pc.bn = pc.pack_rows = mfma_pick_bn(cout);
         pc.cin_pad = (cin + 31) / 32 * 32;
         pc.cout_pad = (cout + pc.bn - 1) / pc.bn * pc.bn;
-        wbytes = sizeof(uint16_t) * mfma_bf16_packed_elems(pc);
-        wbuf.assign(wbytes, 0);
-        mfma_bf16_pack(pc, weight, reinterpret_cast<uint16_t*>(wbuf.data()));
+        pc.wv = dev;
+        pc.w_unscale = bf16 ? 1.f : 1.f / scale;
+        e = hipMalloc(&pc.w, mfma_packed_bytes(pc));
+        if (e == hipSuccess) e = launch_pack_mfma(pc, bf16 ? 1.f : scale, nullptr);
     }
-    // the 64-channel tile's packing, for launches too small for the 128-channel one
-    std::vector<char> abuf;
-    if (pc.impl != CONV_DIRECT && pc.bn == 128) {
-        PlanConv alt = pc;
-        alt.bn = 64;
-        alt.cout_pad = (cout + 63) / 64 * 64;
-        pc.bn_alt = alt.bn;
-        pc.cout_pad_alt = alt.cout_pad;
-        if (pc.impl == CONV_MFMA_F32) {
-            abuf.assign(sizeof(float) * mfma_f32_packed_floats(alt), 0);
-            mfma_f32_pack(alt, weight, reinterpret_cast<float*>(abuf.data()));
-        } else {
-            abuf.assign(sizeof(uint16_t) * mfma_bf16_packed_elems(alt), 0);
-            mfma_bf16_pack(alt, weight, reinterpret_cast<uint16_t*>(abuf.data()));
-        }
-    }
-    bias.assign(pc.cout_pad, 0.f);
+    std::vector<float> bias(pc.cout_pad, 0.f);
     for (int o = 0; o < cout; ++o) bias[o] = bias_in ? bias_in[o] : 0.f;
-    hipError_t e = hipMalloc(&pc.w, wbytes);
     if (e == hipSuccess) e = hipMalloc((void**)&pc.b, sizeof(float) * bias.size());
-    if (e == hipSuccess) e = hipMemcpy(pc.w, wbuf.data(), wbytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess && !abuf.empty()) {
-        e = hipMalloc(&pc.w_alt, abuf.size());
-        if (e == hipSuccess) e = hipMemcpy(pc.w_alt, abuf.data(), abuf.size(), hipMemcpyHostToDevice);
-    }
     if (e == hipSuccess) e = hipMemcpy(pc.b, bias.data(), sizeof(float) * bias.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "uploading weights");
     return DSS_OK;
@@ -294,13 +286,14 @@ static void free_plan_memory(dss_plan* p) {
         for (auto& c : *list) {
             if (c.w) (void)hipFree(c.w);
             if (c.b) (void)hipFree(c.b);
-            if (c.w_alt) (void)hipFree(c.w_alt);
             if (c.w2) (void)hipFree(c.w2);
             c.w = nullptr;
             c.b = nullptr;
-            c.w_alt = nullptr;
             c.w2 = nullptr;
         }
+    for (float* w : p->wraw)
+        if (w) (void)hipFree(w);
+    p->wraw.clear();
     if (p->proj_b) (void)hipFree(p->proj_b);
     p->proj_b = nullptr;
     for (hipEvent_t e : p->events) (void)hipEventDestroy(e);
@@ -341,8 +334,7 @@ static dss_status setup_fusions(dss_plan* p, const dss_layer* layers) {
     if (!a.has_conv || a.has_pool || !b.has_conv || b.has_pool || b.c_h != 1 || b.c_w != 1 || b.cout > 4) return DSS_OK;
     PlanConv& pc = p->convs[L - 2];
     if (pc.impl != CONV_MFMA_F32 && pc.impl != CONV_MFMA_BF16) return DSS_OK;
-    const int rows = std::max(pc.cout_pad, pc.cout_pad_alt);
-    std::vector<float> w2((size_t)rows * 4, 0.f), b2(4, 0.f);
+    std::vector<float> w2((size_t)pc.cout_pad * 4, 0.f), b2(4, 0.f);
     const dss_layer& d = layers[b.desc];
     for (int n = 0; n < b.cin; ++n)
         for (int o = 0; o < b.cout; ++o) {
@@ -386,29 +378,41 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
     const int L = p->chain.L();
     p->convs.resize(L);
     if (dtype == DSS_F32) p->bconvs.resize(L);
-    for (int j = 0; j < L; ++j) {
+    p->wraw.assign(L, nullptr);
+    for (int j = 0; j < L && s == DSS_OK; ++j) {
         const ChainLayer& c = p->chain.layers[j];
         if (!c.has_conv) continue;
         const dss_layer& d = layers[c.desc];
-        s = upload_conv(c.cin, c.cout, c.c_h, c.c_w, c.act, d.weight, d.bias, dtype, p->convs[j]);
+        const int64_t taps = (int64_t)c.c_h * c.c_w;
+        const size_t n = (size_t)c.cout * c.cin * taps;
+        e = hipMalloc((void**)&p->wraw[j], sizeof(float) * n);
+        if (e == hipSuccess) e = hipMemcpy(p->wraw[j], d.weight, sizeof(float) * n, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            s = hip_fail(e, "uploading weights");
+            break;
+        }
+        bool nonfinite = false;
+        const float scale = dtype == DSS_F32 ? weight_scale(d.weight, n, &nonfinite) : 1.f;
+        const WeightView fwd{p->wraw[j], (int64_t)c.cin * taps, taps, 0, nonfinite};
+        s = upload_conv(c.cin, c.cout, c.c_h, c.c_w, c.act, d.weight, fwd, scale, d.bias, dtype, p->convs[j]);
         if (s == DSS_OK && dtype == DSS_F32) {
             // input gradient: w'[i][o][t_h][t_w] = w[o][i][fh-1-t_h][fw-1-t_w]
-            std::vector<float> wt((size_t)c.cin * c.cout * c.c_h * c.c_w);
-            for (int o = 0; o < c.cout; ++o)
-                for (int i = 0; i < c.cin; ++i)
-                    for (int th = 0; th < c.c_h; ++th)
-                        for (int tw = 0; tw < c.c_w; ++tw)
-                            wt[(((size_t)i * c.cout + o) * c.c_h + (c.c_h - 1 - th)) * c.c_w + (c.c_w - 1 - tw)] =
-                                d.weight[(((size_t)o * c.cin + i) * c.c_h + th) * c.c_w + tw];
-            s = upload_conv(c.cout, c.cin, c.c_h, c.c_w, DSS_ACT_NONE, wt.data(), nullptr, dtype, p->bconvs[j]);
-        }
-        if (s != DSS_OK) {
-            free_plan_memory(p);
-            delete p;
-            return s;
+            const WeightView bwd{p->wraw[j], taps, (int64_t)c.cin * taps, 1, nonfinite};
+            s = upload_conv(c.cout, c.cin, c.c_h, c.c_w, DSS_ACT_NONE, d.weight, bwd, scale, nullptr, dtype,
+                            p->bconvs[j]);
         }
     }
-    s = setup_fusions(p, layers);
+    if (s == DSS_OK) s = setup_fusions(p, layers);
+    // the packing kernels ran on the null stream; evaluations may use any
+    if (s == DSS_OK) {
+        e = hipStreamSynchronize(nullptr);
+        if (e != hipSuccess) s = hip_fail(e, "packing weights");
+    }
+    if (s == DSS_OK && dtype == DSS_BF16)   // only the binary32 kernel reads them again
+        for (float*& w : p->wraw) {
+            if (w) (void)hipFree(w);
+            w = nullptr;
+        }
     if (s != DSS_OK) {
         free_plan_memory(p);
         delete p;

@@ -80,6 +80,16 @@ dss_status compute_dilate_geometry(const Chain& ch, dss_dtype dt, int H, int W, 
 // ------------------------------------------------------------------ plan
 enum ConvImpl { CONV_DIRECT = 0, CONV_MFMA_F32 = 1, CONV_MFMA_BF16 = 2 };
 
+// A convolution's weights as given, binary32 on the device: element (n, c, tap) at
+// w[n sn + c sc + tap], or with flip at w[n sn + c sc + taps - 1 - tap] (the
+// input gradient reads the forward weights transposed and flipped).
+struct WeightView {
+    const float* w = nullptr;
+    int64_t sn = 0, sc = 0;
+    int flip = 0;
+    int nonfinite = 0;          // some weight is an infinity or NaN
+};
+
 struct PlanConv {
     ConvImpl impl = CONV_DIRECT;
     int cin = 0, cout = 0, fh = 1, fw = 1, act = 0;
@@ -87,12 +97,14 @@ struct PlanConv {
     int bn = 0, cin_pad = 0;    // MFMA kernels: N tile, padded Cin
     void* w = nullptr;          // device weights in the kernel's layout
     float* b = nullptr;         // device bias [cout_pad], zero padded
-    // MFMA kernels with the 128-channel N tile also keep the weights packed for the
-    // 64-channel tile, used when a launch would leave the GPU short of workgroups
-    void* w_alt = nullptr;
-    int bn_alt = 0, cout_pad_alt = 0;
+    int pack_rows = 0;          // MFMA kernels: output channels per packed weight slice (the plan's bn; a
+                                // launch with a narrower N tile reads parts of the slices)
+    // binary32 MFMA kernel: the weights as given (its non-finite outputs are summed
+    // again from them) and 2^-s of the power of two that their binary16 parts carry
+    WeightView wv;
+    float w_unscale = 1.f;
     // MFMA convolution followed by a folded 1x1 projection: its weights as
-    // [max(cout_pad, cout_pad_alt)][4] binary32 (zero padded), device
+    // [cout_pad][4] binary32 (zero padded), device
     float* w2 = nullptr;
 };
 
@@ -139,6 +151,7 @@ struct dss_plan {
     std::vector<dss::PlanConv> convs;     // one per chain layer (impl unused if no conv)
     std::vector<dss::PlanConv> bconvs;    // binary32 plans: the input-gradient convolutions (transposed,
                                           // flipped filters, no bias, no activation)
+    std::vector<float*> wraw;             // binary32 plans: each convolution's weights as given, device
     // The last chain layer is a 1x1 convolution to at most 4 channels without a
     // pool, after an MFMA convolution without a pool: dense and mixed
     // evaluations fold it into that convolution's epilogue (convs[L-2].w2) and
@@ -245,19 +258,17 @@ hipError_t launch_wgrad(const float* dy, const float* x, int F, int E_h, int E_w
                         int fh, int fw, const WgradPlan& w, float* partial, float* dw, float* db, hipStream_t s);
 hipError_t launch_crop_to_planar(const float* in, int D_w, int C, int H, int W, float* out, hipStream_t s);
 
-// host-side weight packing for the MFMA kernels (conv_mfma.hip)
 // Largest dynamic LDS allocation of a workgroup on the current device.
 size_t device_lds_limit();
 // Lets kern use `bytes` of dynamic LDS on the current device (an opt-in is
 // needed above 64 KB; kept per device and kernel).
 hipError_t allow_dynamic_lds(const void* kern, size_t bytes);
-bool mfma_supports(bool bf16, int fh, int fw);
-int mfma_f32_pick_bn(int cout);
-int mfma_bf16_pick_bn(int cout);
-size_t mfma_f32_packed_floats(const PlanConv& pc);
-void mfma_f32_pack(const PlanConv& pc, const float* w_oihw, float* dst);
-size_t mfma_bf16_packed_elems(const PlanConv& pc);
-void mfma_bf16_pack(const PlanConv& pc, const float* w_oihw, uint16_t* dst);
+// weight packing and tile support of the MFMA kernels (conv_mfma.hip)
+bool mfma_supports(int fh, int fw);
+int mfma_pick_bn(int cout);
+size_t mfma_packed_bytes(const PlanConv& pc);
+// Packs pc.wv (times scale, binary32) into pc.w on the device.
+hipError_t launch_pack_mfma(const PlanConv& pc, float scale, hipStream_t s);
 
 uint16_t host_f32_to_bf16(float f);
 
