@@ -195,6 +195,7 @@ constexpr int kKC = 32;               // positions per chunk
 constexpr int kWP = kWT + 32;         // LDS row pitch in floats: the two half-waves of a read
                                       // (rows p and p + 1) hit disjoint banks
 constexpr int kMaxTT = 8;             // taps of one filter row per workgroup
+constexpr int kMaxSplitTT = 7;        // the same for the binary16-part kernel (accumulators and shifted operands)
 constexpr int kMaxPackedTT = 4;       // MFMA tiles per wave in the packed (narrow-layer) mode
 
 static size_t wgrad_lds_bytes(int tt) { return 2 * (size_t)(kKC + kKC + tt - 1) * kWP * sizeof(float); }
@@ -223,8 +224,8 @@ static size_t wgrad_lds_bytes(int tt) { return 2 * (size_t)(kKC + kKC + tt - 1) 
 template <bool VEC, int TT, bool PACKED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_mfma_kernel(
     const float* __restrict__ dy, const float* __restrict__ x, int E_h, int E_w, int U_h, int U_w, int Cout, int Cin,
-    int fh, int fw, int Q, int nchunks, int otiles, int itiles, int ntg, int splits, int cpt,
-    float* __restrict__ partial, float* __restrict__ bias_partial) {
+    int fh, int fw, int Q, int nchunks, int chunk_mul, int otiles, int itiles, int ntg, int splits, int cpt,
+    const uint32_t* __restrict__ flags, float* __restrict__ partial, float* __restrict__ bias_partial) {
     constexpr int RB = kKC + TT - 1;              // staged x rows per chunk (unpacked; bounds the buffer)
     extern __shared__ __attribute__((aligned(16))) float wl[];
     auto lds_a = [&](int buf) { return wl + buf * (kKC * kWP); };                  // dy rows
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int q8 = total / 8, r8 = total % 8;
     int bid = xcd < r8 ? xcd * (q8 + 1) + slot : r8 * (q8 + 1) + (xcd - r8) * q8 + slot;
+    if (flags && !flags[bid]) return;             // after wgrad_split_kernel: only the workgroups it marked
     const int ot = bid % otiles;
     bid /= otiles;
     const int it = bid % itiles;
@@ -250,7 +252,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
     const int tw0 = tg * span;
     const int ntt = min(span, fw - tw0);          // taps of this group
     const int rows_b = kKC + span - 1;            // staged x rows per chunk
-    const int c0 = (int)((int64_t)nchunks * split / splits), c1 = (int)((int64_t)nchunks * (split + 1) / splits);
+    const int c0 = (int)((int64_t)nchunks * split / splits) * chunk_mul;
+    const int c1 = (int)((int64_t)nchunks * (split + 1) / splits) * chunk_mul;
     const int o0 = ot * kWT, i0 = it * kWT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1, half = lane >> 5, l32 = lane & 31;
@@ -366,6 +369,315 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
     }
 }
 
+// ------------------------------------------------------------------ wgrad on binary16 parts
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+constexpr int kSC = 64;                    // positions per chunk
+constexpr int kSRow = 2 * kWT + 16;        // LDS bytes per staged position and part (the 16 bytes put the four
+                                           // rows of a transposing read on different banks)
+constexpr int kSRowsX = kSC + 8;           // staged x positions (taps read up to 7 further on)
+constexpr int kSPlaneA = kSC * kSRow, kSPlaneB = kSRowsX * kSRow;
+constexpr int kSBuf = 2 * (kSPlaneA + kSPlaneB);   // hi and lo parts of dy and x
+constexpr int kSLds = 2 * kSBuf + 64;              // two buffers and the control words
+
+// n / d for 0 <= n < 2^31 and a divisor of at least 2 (multiplication by its rounded-up reciprocal)
+struct FastDiv {
+    uint32_t mul, shift;
+};
+static FastDiv fast_div(uint32_t d) {
+    uint32_t l = 1;
+    while ((1ull << l) < d) ++l;
+    return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), l - 1};
+}
+__device__ __forceinline__ uint32_t div_by(uint32_t n, FastDiv f) { return __umulhi(n, f.mul) >> f.shift; }
+
+// The same weight gradient (unpacked layers, channels in fours) with every operand
+// split into two binary16 numbers under a power-of-two scale, three
+// v_mfma_f32_16x16x32_f16 per product (see conv_mfma.hip): the contraction runs
+// over the positions, 32 per issue.  The matrix instruction wants eight
+// consecutive positions of one channel per lane; the chunk is staged as it lies in
+// memory, positions of 64 channels, and read by the transposing LDS loads
+// (ds_read_b64_tr_b16: four positions of a lane's channel).  A lane reads 16
+// positions of x once and shifts them in registers for every tap.
+//
+// One scale per operand and workgroup, since a product's positions must share it:
+// the first chunk's largest magnitude goes to [2^12, 2^13), and a later chunk that
+// would exceed binary16 lowers the scale (the accumulators follow, exactly).  The
+// values of a chunk are converted with the scale at hand; a thread that meets one
+// too large says so in LDS, and after the barrier that the chunk needs anyway all
+// threads convert it again, from their registers.  Workgroups that met an infinity
+// or NaN set their flag, and the binary32 kernel computes their sums again.
+template <int TT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_split_kernel(
+    const float* __restrict__ dy, const float* __restrict__ x, int E_h, int E_w, int U_w, int Cout, int Cin, int fh,
+    int fw, int Q, int nchunks, int otiles, int itiles, int ntg, int splits, FastDiv by_row, FastDiv by_frag,
+    uint32_t* __restrict__ flags, float* __restrict__ partial, float* __restrict__ bias_partial) {
+    extern __shared__ __attribute__((aligned(16))) float wl[];
+    char* const lds = reinterpret_cast<char*>(wl);
+    // control words: largest dy and x that did not fit, for chunks of even ([0], [1]) and
+    // odd ([2], [3]) number (a wave may be a barrier ahead of another's reading them), and
+    // [4] whether a value was not finite
+    uint32_t* const ctl = reinterpret_cast<uint32_t*>(lds + 2 * kSBuf);
+    const int total = gridDim.x;
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int q8 = total / 8, r8 = total % 8;
+    const int id = xcd < r8 ? xcd * (q8 + 1) + slot : r8 * (q8 + 1) + (xcd - r8) * q8 + slot;
+    int bid = id;
+    const int ot = bid % otiles;
+    bid /= otiles;
+    const int it = bid % itiles;
+    bid /= itiles;
+    const int tg = bid % ntg;
+    bid /= ntg;
+    const int th = bid % fh;
+    const int split = bid / fh;
+    const int tw0 = tg * TT;
+    const int ntt = min(TT, fw - tw0);
+    const int c0 = (int)((int64_t)nchunks * split / splits), c1 = (int)((int64_t)nchunks * (split + 1) / splits);
+    const int o0 = ot * kWT, i0 = it * kWT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1, grp = lane >> 4, l16 = lane & 15;
+    const int s_col = (tid & 15) * 4, s_row = tid >> 4;          // staging: 16 float4 per row, 16 rows per pass
+
+    floatx4 acc[TT][2][2];
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[t][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    constexpr int NA = kSC / 16, NB = (kSC + TT - 1 + 15) / 16;
+    floatx4 ra[NA], rb[NB];
+    const bool col_a = o0 + s_col < Cout, col_b = i0 + s_col < Cin;
+    auto load_chunk = [&](int c) {
+        const int qc = c * kSC + s_row;
+#pragma unroll
+        for (int k = 0; k < NA; ++k) {
+            const int q = qc + 16 * k;
+            const int r = (int)div_by((uint32_t)q, by_row), xx = q - r * U_w;   // r = f E_h + y
+            const float* src = dy + ((int64_t)r * E_w + xx) * Cout + o0 + s_col;
+            ra[k] = q < Q && xx < E_w && col_a ? *reinterpret_cast<const floatx4*>(src) : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const int q = qc + 16 * k + tw0;
+            const int f = (int)div_by((uint32_t)q, by_frag);
+            const float* src = x + ((int64_t)q + (int64_t)(f * (fh - 1) + th) * U_w) * Cin + i0 + s_col;
+            rb[k] = q < Q && col_b && (16 * k + 15 < kSC + TT - 1 || s_row + 16 * k < kSC + TT - 1)
+                        ? *reinterpret_cast<const floatx4*>(src)
+                        : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    // largest magnitude among a thread's values, as bits
+    auto top_bits = [&](const floatx4* r, int n) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(r[k][e]) & 0x7fffffffu);
+        if (m >= 0x7f800000u) {          // the largest finite one
+            ctl[4] = 1u;
+            m = 0;
+            for (int k = 0; k < n; ++k)
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t b = __float_as_uint(r[k][e]) & 0x7fffffffu;
+                    m = max(m, b < 0x7f800000u ? b : 0u);
+                }
+        }
+        return m;
+    };
+    // power of two that takes a largest magnitude with these bits into [2^12, 2^13), at most 2^100
+    auto scale_of = [](uint32_t bits) {
+        return __uint_as_float(min((266u << 23) - (bits & 0x7f800000u), 227u << 23));
+    };
+    // The matrix instruction rounds its sums down a little (the mean error of a sum
+    // is negative, whatever its sign), which over the positions of all splits would
+    // add up: 1.1e-6 of the gradient over 2^20 positions, beside 5e-7 of scatter.
+    // Every other split therefore sums -dy x, and its sums are negated back.
+    const float sign = split & 1 ? -1.f : 1.f;
+    float sa = 1.f, sb = 1.f;
+    auto store_part = [&](char* plane, int plane_bytes, int row, floatx4 r, float scale) {
+        f16x4 h, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float v = r[e] * scale;
+            h[e] = (_Float16)v;
+            l[e] = (_Float16)(v - (float)h[e]);
+        }
+        char* dst = plane + row * kSRow + s_col * 2;
+        *reinterpret_cast<u32x2*>(dst) = __builtin_bit_cast(u32x2, h);
+        *reinterpret_cast<u32x2*>(dst + plane_bytes) = __builtin_bit_cast(u32x2, l);
+    };
+    auto store_chunk = [&](int buf) {
+        char* A = lds + buf * kSBuf;
+        char* B = A + 2 * kSPlaneA;
+#pragma unroll
+        for (int k = 0; k < NA; ++k) store_part(A, kSPlaneA, s_row + 16 * k, ra[k], sa);
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (s_row + 16 * k < kSRowsX) store_part(B, kSPlaneB, s_row + 16 * k, rb[k], sb);
+    };
+
+    // db[o] = sum_p dy[p][o]: the workgroups of the first input tile, tap row and tap group add their dy rows
+    const bool do_bias = it == 0 && tg == 0 && th == 0;
+    floatx4 bsum = {0.f, 0.f, 0.f, 0.f};
+    auto add_bias = [&] {
+        if (do_bias) {
+#pragma unroll
+            for (int k = 0; k < NA; ++k) bsum += ra[k];
+        }
+    };
+
+    if (tid < 5) ctl[tid] = 0u;
+    __syncthreads();
+    if (c0 < c1) {
+        load_chunk(c0);
+        uint32_t ma = top_bits(ra, NA), mb = top_bits(rb, NB);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            ma = max(ma, (uint32_t)__shfl_xor((int)ma, d));
+            mb = max(mb, (uint32_t)__shfl_xor((int)mb, d));
+        }
+        if (lane == 0) {
+            atomicMax(&ctl[0], ma);
+            atomicMax(&ctl[1], mb);
+        }
+        __syncthreads();
+        sa = sign * scale_of(ctl[0]);
+        sb = scale_of(ctl[1]);
+        __syncthreads();
+        if (tid < 2) ctl[tid] = 0u;
+        store_chunk(0);
+        add_bias();
+    }
+    __syncthreads();
+    // transposing reads: lane j of group g reads positions 8 g + j / 4, channels 4 (j % 4) .. + 3
+    // of a 16-channel tile, and receives four positions of channel j
+    const int tr_off = (8 * grp + (l16 >> 2)) * kSRow + (l16 & 3) * 8;
+    auto tr_read = [&](const char* p) {
+        return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+    };
+    for (int c = c0; c < c1; ++c) {
+        const int buf = (c - c0) & 1;
+        const bool more = c + 1 < c1;
+        if (more) load_chunk(c + 1);
+        const char* A = lds + buf * kSBuf + tr_off + wm * 64;
+        const char* B = lds + buf * kSBuf + 2 * kSPlaneA + tr_off + wn * 64;
+#pragma unroll
+        for (int ks = 0; ks < kSC / 32; ++ks) {
+            f16x8 a[2][2];
+#pragma unroll
+            for (int oi = 0; oi < 2; ++oi)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const char* src = A + p * kSPlaneA + ks * 32 * kSRow + oi * 32;
+                    const u32x2 lo = tr_read(src), hi = tr_read(src + 4 * kSRow);
+                    a[oi][p] = __builtin_bit_cast(f16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+                }
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii) {
+                // 16 positions of the lane's channel per part, and the same one position on
+                uint32_t even[2][8], odd[2][8];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const char* src = B + p * kSPlaneB + ks * 32 * kSRow + ii * 32;
+#pragma unroll
+                    for (int k = 0; k < (TT > 1 ? 4 : 2); ++k) {
+                        const u32x2 v = tr_read(src + 4 * k * kSRow);
+                        even[p][2 * k] = v[0];
+                        even[p][2 * k + 1] = v[1];
+                    }
+                    if constexpr (TT > 1) {
+#pragma unroll
+                        for (int k = 0; k < 7; ++k)
+                            odd[p][k] = __builtin_amdgcn_alignbit(even[p][k + 1], even[p][k], 16);
+                    }
+                }
+                auto tap = [&](int t, int p) {
+                    const uint32_t* r = t & 1 ? odd[p] : even[p];
+                    const int k = t >> 1;
+                    return __builtin_bit_cast(f16x8, u32x4{r[k], r[k + 1], r[k + 2], r[k + 3]});
+                };
+                // the smallest products first
+#pragma unroll
+                for (int t0 = 0; t0 < TT; t0 += 2)
+#pragma unroll
+                    for (int pr = 0; pr < 3; ++pr)
+#pragma unroll
+                        for (int t = t0; t < (t0 + 2 < TT ? t0 + 2 : TT); ++t)
+#pragma unroll
+                            for (int oi = 0; oi < 2; ++oi)
+                                acc[t][oi][ii] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                    a[oi][pr == 0], tap(t, pr == 1), acc[t][oi][ii], 0, 0, 0);
+            }
+        }
+        if (more) {
+            const uint32_t ma = top_bits(ra, NA), mb = top_bits(rb, NB);
+            if (__uint_as_float(ma) * fabsf(sa) >= 65504.f) atomicMax(&ctl[2 * buf], ma);
+            if (__uint_as_float(mb) * sb >= 65504.f) atomicMax(&ctl[2 * buf + 1], mb);
+            store_chunk(buf ^ 1);
+            add_bias();
+        }
+        __syncthreads();
+        const uint32_t na = ctl[2 * buf], nb = ctl[2 * buf + 1];
+        if (na | nb) {                        // the chunk does not fit its scale: lower it, convert again
+            const float fa = na ? sign * scale_of(na) : sa, fb = nb ? scale_of(nb) : sb;
+            const float down = (fa / sa) * (fb / sb);
+            sa = fa;
+            sb = fb;
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+#pragma unroll
+                for (int oi = 0; oi < 2; ++oi)
+#pragma unroll
+                    for (int ii = 0; ii < 2; ++ii) acc[t][oi][ii] *= down;
+            __syncthreads();                  // everyone has read the control words
+            if (tid < 2) ctl[2 * buf + tid] = 0u;
+            store_chunk(buf ^ 1);
+            __syncthreads();
+        }
+    }
+
+    if (tid == 0) flags[id] = ctl[4];
+    if (do_bias) {
+        // rows s_row of the 16 column quads, added in order
+        __syncthreads();
+        *reinterpret_cast<floatx4*>(lds + tid * 16) = bsum;
+        __syncthreads();
+        if (tid < kWT && o0 + tid < Cout) {
+            const float* v = wl + (tid >> 2) * 4 + (tid & 3);
+            float s = 0.f;
+            for (int k = 0; k < 16; ++k) s += v[k * 64];
+            bias_partial[(size_t)split * Cout + o0 + tid] = s;
+        }
+    }
+    const float ua = 1.f / sa, ub = 1.f / sb;
+    const int taps = fh * fw;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+        if (t >= ntt) continue;
+        float* dst = partial + ((size_t)split * taps + th * fw + tw0 + t) * Cout * Cin;
+#pragma unroll
+        for (int oi = 0; oi < 2; ++oi)
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii) {
+                const int i = i0 + wn * 32 + ii * 16 + l16;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int o = o0 + wm * 32 + oi * 16 + grp * 4 + v;
+                    if (o < Cout && i < Cin) dst[(size_t)o * Cin + i] = acc[t][oi][ii][v] * ua * ub;
+                }
+            }
+    }
+}
+
 // dW[o][i][th][tw] = sum over splits (in order) of partial[s][tap][o][i], and
 // db[o] = sum over splits (in order) of bias_partial[s][o].
 __global__ __launch_bounds__(kBT) void wgrad_reduce_kernel(const float* __restrict__ partial,
@@ -393,6 +705,8 @@ __global__ __launch_bounds__(kBT) void wgrad_reduce_kernel(const float* __restri
 
 WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw) {
     WgradPlan w;
+    // the binary16-part kernel: unpacked layers, whole float4 channel groups, and rows that its division takes
+    w.split = Cin > kWT / 2 && Cout % 4 == 0 && Cin % 4 == 0 && E_w + fw - 1 >= 2;
     if (Cin <= kWT / 2) {
         // packed: cpt columns per tap, g taps per tile; at most kMaxPackedTT tiles,
         // the fewest MFMA tiles per row (ntg * tt), then the most taps per group
@@ -412,7 +726,7 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
     } else {
         // the largest group of taps (at most kMaxTT) whose ragged last group wastes
         // at most a tenth of the row's MFMA work
-        for (int tt = std::min(fw, kMaxTT); tt >= 1; --tt) {
+        for (int tt = std::min(fw, w.split ? kMaxSplitTT : kMaxTT); tt >= 1; --tt) {
             const int ntg = (fw + tt - 1) / tt;
             if (10 * (ntg * tt - fw) <= fw) {
                 w.tt = tt;
@@ -422,7 +736,8 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
         }
     }
     w.positions = (int64_t)F * E_h * (E_w + fw - 1);
-    w.nchunks = (w.positions + kKC - 1) / kKC;
+    const int64_t chunk = w.split ? kSC : kKC;
+    w.nchunks = (w.positions + chunk - 1) / chunk;
     w.otiles = (Cout + kWT - 1) / kWT;
     w.itiles = w.packed ? 1 : (Cin + kWT - 1) / kWT;
     const int64_t base = (int64_t)w.otiles * w.itiles * fh * w.ntg;
@@ -432,7 +747,7 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
     // least 64 chunks, so that a workgroup's prologue and partial-sum stores stay
     // small against its loop (measured on the 512 x 512 frame: 8 -> 64 chunks
     // makes its weight gradients 6.6 -> 5.5 ms).
-    const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(4096, w.nchunks / 64));
+    const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(4096, w.nchunks * chunk / (64 * kKC)));
     const int64_t lo = std::min(max_splits, std::max<int64_t>(1, (512 * 8 + base - 1) / base));
     const int64_t hi = std::min(max_splits, 2 * lo);
     int64_t best = lo;
@@ -447,22 +762,36 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
     }
     w.splits = (int)best;
     w.partial_floats = (int64_t)w.splits * fh * fw * Cout * Cin;
-    w.bias_partial_floats = (int64_t)w.splits * Cout;
+    w.bias_partial_floats = (int64_t)w.splits * Cout + (w.split ? base * w.splits : 0);   // and a flag per workgroup
     return w;
 }
 
 template <bool VEC, int TT, bool PACKED>
 static hipError_t run_wgrad(const float* dy, const float* x, int E_h, int E_w, int U_h, int U_w, int Cout, int Cin,
                             int fh, int fw, const WgradPlan& w, float* partial, float* bpart, hipStream_t s) {
+    const int64_t nblocks = (int64_t)w.otiles * w.itiles * fh * w.ntg * w.splits;
+    if (nblocks >= (1ll << 31)) return hipErrorInvalidConfiguration;
+    uint32_t* flags = nullptr;
+    if constexpr (VEC && !PACKED && TT <= kMaxSplitTT) {
+        if (w.split) {
+            auto kern = wgrad_split_kernel<TT>;
+            hipError_t e = allow_dynamic_lds((const void*)kern, kSLds);
+            if (e != hipSuccess) return e;
+            flags = reinterpret_cast<uint32_t*>(bpart + (int64_t)w.splits * Cout);
+            kern<<<dim3((unsigned)nblocks), 256, kSLds, s>>>(
+                dy, x, E_h, E_w, U_w, Cout, Cin, fh, fw, (int)w.positions, (int)w.nchunks, w.otiles, w.itiles, w.ntg,
+                w.splits, fast_div((uint32_t)U_w), fast_div((uint32_t)(E_h * U_w)), flags, partial, bpart);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
     auto kern = wgrad_mfma_kernel<VEC, TT, PACKED>;
     const size_t lds = wgrad_lds_bytes(TT);
     hipError_t e = allow_dynamic_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
-    const int64_t nblocks = (int64_t)w.otiles * w.itiles * fh * w.ntg * w.splits;
-    if (nblocks >= (1ll << 31)) return hipErrorInvalidConfiguration;
     kern<<<dim3((unsigned)nblocks), 256, lds, s>>>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, (int)w.positions,
-                                                   (int)w.nchunks, w.otiles, w.itiles, w.ntg, w.splits, w.cpt,
-                                                   partial, bpart);
+                                                   (int)w.nchunks, w.split ? kSC / kKC : 1, w.otiles, w.itiles, w.ntg,
+                                                   w.splits, w.cpt, flags, partial, bpart);
     return hipGetLastError();
 }
 
@@ -497,7 +826,7 @@ hipError_t launch_wgrad(const float* dy, const float* x, int F, int E_h, int E_w
     (void)F;
     // positions and chunks are 32-bit in the kernel
     const int span = w.packed ? w.tt * (kWT / w.cpt) : w.tt;   // taps per group
-    if (w.positions + span + kKC >= (1ll << 31) || U_w != E_w + fw - 1 || U_h != E_h + fh - 1)
+    if (w.positions + span + kSC >= (1ll << 31) || U_w != E_w + fw - 1 || U_h != E_h + fh - 1)
         return hipErrorInvalidConfiguration;
     float* bpart = partial + w.partial_floats;
     const bool vec = Cout % 4 == 0 && Cin % 4 == 0;

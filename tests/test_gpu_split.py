@@ -131,3 +131,42 @@ def test_bits_do_not_depend_on_the_surroundings():
     out, _ = gpu_dense(w.layers, w.x, 2)
     alone, _ = gpu_dense(w.layers, np.ascontiguousarray(inner), 2)
     np.testing.assert_array_equal(out[:, 4:4 + alone.shape[1], 6:6 + alone.shape[2]], alone)
+
+
+def _weight_gradient(x, G, fh, fw):
+    """dW[o][i][a][b] = sum_p G[o][p] x[i][p + (a, b)] in 64 bits."""
+    eh, ew = G.shape[1:]
+    g = G.astype(np.float64).reshape(G.shape[0], -1)
+    out = np.empty((G.shape[0], x.shape[0], fh, fw))
+    for a in range(fh):
+        for b in range(fw):
+            out[:, :, a, b] = g @ x[:, a:a + eh, b:b + ew].astype(np.float64).reshape(x.shape[0], -1).T
+    return out
+
+
+# taps per group 1..7 (the kernel's instantiations, 8 in two groups of 4), channels past one 64-wide tile, several
+# splits; "rising": magnitudes that grow by 1e8 along the signal after a zero start, so the scales are lowered on the
+# way; "inf" / "nan": one such sample
+@pytest.mark.parametrize("fw", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("data", ["plain", "rising", "inf", "nan"])
+def test_weight_gradient_parts(fw, data):
+    import torch
+    cin, cout, fh, H, W = (68, 72, 2, 50, 61) if fw % 2 else (36, 64, 1, 70, 83)
+    w = wl.custom([("conv", cin, cout, fh, fw, "none")], cin, H, W, seed=70 + fw, value_kind="normal")
+    rng = np.random.default_rng(71)
+    G = rng.standard_normal((cout, H - fh + 1, W - fw + 1)).astype(np.float32)
+    if data == "rising":
+        w.x *= np.geomspace(1e-4, 1e4, H, dtype=np.float32)[None, :, None]
+        G *= np.geomspace(1e-5, 1e3, G.shape[1], dtype=np.float32)[None, :, None]
+        w.x[:, :4] = 0
+        G[:, :3] = 0
+    if data in ("inf", "nan"):
+        w.x[5, H // 2, W // 2] = np.inf if data == "inf" else np.nan
+    plan = dss.Plan(w.layers, 2, cin)
+    gw, gb, _ = plan.backward(torch.from_numpy(w.x).cuda(), torch.from_numpy(G).cuda(), with_signal_grad=False)
+    torch.cuda.synchronize()
+    got = plan.split_grads(gw, gb)[0][0].cpu().numpy().astype(np.float64)
+    ref = _weight_gradient(w.x, G, fh, fw)
+    check(got, ref, "dW fw %d %s" % (fw, data))
+    db = G.astype(np.float64).sum((1, 2))
+    assert np.abs(gb.cpu().numpy() - db).max() <= F32_TOL * max(np.abs(db).max(), np.abs(G).max())
