@@ -379,17 +379,23 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
     p->convs.resize(L);
     if (dtype == DSS_F32) p->bconvs.resize(L);
     p->wraw.assign(L, nullptr);
+    bool packed = false;
     for (int j = 0; j < L && s == DSS_OK; ++j) {
         const ChainLayer& c = p->chain.layers[j];
         if (!c.has_conv) continue;
         const dss_layer& d = layers[c.desc];
         const int64_t taps = (int64_t)c.c_h * c.c_w;
         const size_t n = (size_t)c.cout * c.cin * taps;
-        e = hipMalloc((void**)&p->wraw[j], sizeof(float) * n);
-        if (e == hipSuccess) e = hipMemcpy(p->wraw[j], d.weight, sizeof(float) * n, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            s = hip_fail(e, "uploading weights");
-            break;
+        // the weights as given: what the MFMA layouts are packed from
+        if (choose_impl(c.cin, c.cout, c.c_h, c.c_w, dtype) != CONV_DIRECT ||
+            (dtype == DSS_F32 && choose_impl(c.cout, c.cin, c.c_h, c.c_w, dtype) != CONV_DIRECT)) {
+            packed = true;
+            e = hipMalloc((void**)&p->wraw[j], sizeof(float) * n);
+            if (e == hipSuccess) e = hipMemcpy(p->wraw[j], d.weight, sizeof(float) * n, hipMemcpyHostToDevice);
+            if (e != hipSuccess) {
+                s = hip_fail(e, "uploading weights");
+                break;
+            }
         }
         bool nonfinite = false;
         const float scale = dtype == DSS_F32 ? weight_scale(d.weight, n, &nonfinite) : 1.f;
@@ -404,7 +410,7 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
     }
     if (s == DSS_OK) s = setup_fusions(p, layers);
     // the packing kernels ran on the null stream; evaluations may use any
-    if (s == DSS_OK) {
+    if (s == DSS_OK && packed) {
         e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) s = hip_fail(e, "packing weights");
     }
@@ -774,12 +780,21 @@ dss_status eval_prepare(dss_plan_t plan, const void* signal, const void* out, in
 dss_status eval_run(dss_plan_t plan, const Geom& G, const void* signal, float* out, char* ws, hipStream_t stream,
                     bool timed) {
     Timer T(plan, stream, timed);
+    const Chain& ch = plan->chain;
+    FusedChain fc;
+    if (G.ell == 0 && plan->dtype == DSS_F32 && fused_plan(ch, plan->convs, G.out_h, G.out_w, G.conv_flops, &fc)) {
+        const double bytes = 4.0 * ((double)ch.in_c * G.H * G.W + (double)ch.out_c() * G.out_h * G.out_w);
+        hipError_t e = T.run("dense_fused", ch.L(), G.conv_flops, bytes, [&] {
+            return launch_fused_chain(fc, (const float*)signal, G.H, G.W, out, G.out_h, G.out_w, stream);
+        });
+        if (e != hipSuccess) return hip_fail(e, "fused evaluation launch");
+        return DSS_OK;
+    }
     void* cur = nullptr;
     dss_dtype cdt;
     int part_nbs = 0;
     dss_status s = run_chain(plan, G, signal, plan->chain.L(), ws, stream, T, &cur, &cdt, true, &part_nbs);
     if (s != DSS_OK) return s;
-    const Chain& ch = plan->chain;
     // Defrag_{k*_L / k*_ell}, then keep the first out_h x out_w samples (this is
     // Trim_r of the dense evaluation and the final trimming of the stuffing mode)
     const int Gh = ch.K_h() / G.step_h, Gw = ch.K_w() / G.step_w;

@@ -136,6 +136,25 @@ struct WgradPlan {
                                        // kernel's flags, one word per workgroup)
 };
 
+// A small network evaluated in one launch (chain_fused.hip): per chain layer the
+// regions of one output tile (entering, after the convolution, after the pool) and
+// the direct kernel's weights.
+constexpr int kMaxFused = 8;
+struct FusedLayer {
+    const float* w = nullptr;
+    const float* b = nullptr;
+    int cin = 0, cout = 0, cout_pad = 0, cob = 1, fh = 1, fw = 1, act = 0, has_conv = 0;
+    int k_h = 1, k_w = 1, dil_h = 1, dil_w = 1;
+    int in_h = 0, in_w = 0, e_h = 0, e_w = 0, u_h = 0, u_w = 0;
+    int w_at = 0;               // the layer's weights in LDS, floats after the first layer's
+};
+struct FusedChain {
+    int n = 0, in_c = 0, TH = 0, TW = 0, tiles_x = 0;
+    int buf_floats[2] = {0, 0};
+    size_t lds_bytes = 0;
+    FusedLayer L[kMaxFused];
+};
+
 struct LaunchRec {
     const char* name;
     int layer;
@@ -246,6 +265,14 @@ hipError_t launch_to_planar(dss_dtype dt, const void* in, int F, int h, int w, i
                             hipStream_t s);
 hipError_t launch_frag_planar(int elem_bytes, bool inverse, const void* in, int k_h, int k_w, int S_h,
                               int S_w, int C, int H, int W, void* out, hipStream_t s);
+
+// The dense evaluation of a small binary32 network in one launch: whether the chain
+// (with these convolutions) on an out_h x out_w output grid is one that is faster
+// that way, and its plan; and the launch (signal planar, out planar).
+bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, int out_w, double conv_flops,
+                FusedChain* fc);
+hipError_t launch_fused_chain(const FusedChain& fc, const float* signal, int H, int W, float* out, int out_h, int out_w,
+                              hipStream_t s);
 
 // backward (backward.hip)
 hipError_t launch_frag_scatter_grad(const float* g, int C, int O_h, int O_w, int K_h, int K_w, int U_h, int U_w,
