@@ -1201,6 +1201,7 @@ extern "C" dss_status dss_backward_dense(dss_plan_t plan, const void* signal, in
 
     // upstream gradient into the final fragment layout (transpose of Defrag + Trim)
     int cur = 0;
+    bool act_done = false;           // gb[cur] has been through the layer's activation already
     e = T.run("frag_scatter_grad", L + 1, 0.0, 0.0, [&] {
         return launch_frag_scatter_grad(grad_out, ch.out_c(), G.out_h, G.out_w, ch.K_h(), ch.K_w(), G.L.back().U_h,
                                         G.L.back().U_w, gb[cur], stream);
@@ -1218,16 +1219,33 @@ extern "C" dss_status dss_backward_dense(dss_plan_t plan, const void* signal, in
             });
             if (e != hipSuccess) return hip_fail(e, "pool_frag_backward launch");
             cur ^= 1;
-        } else if (c.act != DSS_ACT_NONE) {
+        } else if (c.act != DSS_ACT_NONE && !act_done) {
             const int64_t n = (int64_t)Fin * lg.E_h * lg.E_w * c.cout;
             e = T.run("act_backward", j, 0.0, 0.0,
                       [&] { return launch_act_backward(gb[cur], Cv(j), n, c.act, gb[cur ^ 1], stream); });
             if (e != hipSuccess) return hip_fail(e, "act_backward launch");
             cur ^= 1;
         }
+        act_done = false;
         if (!c.has_conv) continue;   // the pool backward produced the gradient of A_{j-1}
         const double fl = 2.0 * Fin * (double)lg.E_h * lg.E_w * c.cout * (double)c.cin * c.c_h * c.c_w;
         const WgradPlan& wp = B.wg[j];
+        // a 1x1 layer to few outputs after a convolution without a pool: weight gradient, input gradient and
+        // that convolution's activation in one pass, bound by memory (whatever the extent: the three steps it
+        // replaces are too, over three times the bytes)
+        if (j > 1 && c.c_h == 1 && c.c_w == 1 && c.cout <= 4 && c.cin % 4 == 0 && ch.layers[j - 2].has_conv &&
+            !ch.layers[j - 2].has_pool && plan->convs[j - 1].impl == CONV_DIRECT &&
+            plan->bconvs[j - 1].impl == CONV_DIRECT) {
+            e = T.run("wgrad_mfma", j, 2.0 * fl, 0.0, [&] {   // the name of every weight gradient's record
+                return launch_narrow_backward(gb[cur], A(j - 1), plan->convs[j - 1], (int64_t)Fin * lg.E_h * lg.E_w,
+                                              ch.layers[j - 2].act, wp, wpart, gb[cur ^ 1], grad_weight + B.wofs[j],
+                                              grad_bias + B.bofs[j], stream);
+            });
+            if (e != hipSuccess) return hip_fail(e, "backward launch of a 1x1 layer");
+            cur ^= 1;
+            act_done = true;
+            continue;
+        }
         e = T.run("wgrad_mfma", j, fl, 0.0, [&] {
             return launch_wgrad(gb[cur], A(j - 1), Fin, lg.E_h, lg.E_w, lg.Uin_h, lg.Uin_w, c.cout, c.cin, c.c_h, c.c_w,
                                 wp, wpart, grad_weight + B.wofs[j], grad_bias + B.bofs[j], stream);

@@ -285,6 +285,10 @@ hipError_t launch_pad_grad(const float* in, int F, int E_h, int E_w, int C, int 
 WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw);
 hipError_t launch_wgrad(const float* dy, const float* x, int F, int E_h, int E_w, int U_h, int U_w, int Cout, int Cin,
                         int fh, int fw, const WgradPlan& w, float* partial, float* dw, float* db, hipStream_t s);
+// Backward of a 1x1 convolution to at most 4 channels (on the direct kernel, cin in
+// fours): dw, db and dx = the input's gradient times act'(a).  partial holds wp's sums.
+hipError_t launch_narrow_backward(const float* g, const float* a, const PlanConv& pc, int64_t npos, int act,
+                                  const WgradPlan& wp, float* partial, float* dx, float* dw, float* db, hipStream_t s);
 hipError_t launch_crop_to_planar(const float* in, int D_w, int C, int H, int W, float* out, hipStream_t s);
 
 // Largest dynamic LDS allocation of a workgroup on the current device.

@@ -1,4 +1,4 @@
-"""GPU parity of two backward paths at their edges, on integer data that every summation order computes exactly
+"""GPU parity of two backward kernels at their edges, on integer data that every summation order computes exactly
 (all partial sums below 2^23, ties in the maxima decided by the shared first-maximum rule): the strip walk of the
 2 x 2 pool's gradient (one to several strips of 16 rows, with remainders), and the one-pass backward of a 1x1 layer
 to 1..4 outputs (channel counts of 1, 3, 9 and 33 quads of lanes, with and without the previous layer's ReLU)."""
