@@ -319,7 +319,7 @@ static size_t wgrad_lds_bytes(int tt) { return 2 * (size_t)(kKC + kKC + tt - 1) 
 // of the group reads its operand rows t_w further on in LDS -- TT times fewer
 // global reads than one workgroup per tap.
 //
-// PACKED (layers with at most 32 input channels): the 64 columns of an MFMA
+// PACKED (narrow layers, at most 32 input channels): the 64 columns of an MFMA
 // tile hold g = 64 / cpt taps of cpt channels each (cpt: Cin rounded up to a
 // power of two, at least 4), column j being tap j / cpt and channel j % cpt, so
 // a narrow layer does not spend 64-column tiles on a few channels.  Tile t of a
@@ -809,9 +809,12 @@ __global__ __launch_bounds__(kBT) void wgrad_reduce_kernel(const float* __restri
 
 WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw) {
     WgradPlan w;
-    // the binary16-part kernel: unpacked layers, whole float4 channel groups, and rows that its division takes
-    w.split = Cin > kWT / 2 && Cout % 4 == 0 && Cin % 4 == 0 && E_w + fw - 1 >= 2;
-    if (Cin <= kWT / 2) {
+    // the binary16-part kernel: whole float4 channel groups, and rows that its division takes
+    // (more than 16 input channels: at 32 its tile is half padding and still faster than two taps side by
+    // side on the binary32 instruction, 0.25 against 0.44 ms for the 5x5 32 -> 64 layer of a 512 x 512
+    // signal; at 16 four taps fill that one's tile)
+    w.split = Cin > kWT / 4 && Cout % 4 == 0 && Cin % 4 == 0 && E_w + fw - 1 >= 2;
+    if (Cin <= kWT / 2 && !w.split) {
         // packed: cpt columns per tap, g taps per tile; at most kMaxPackedTT tiles,
         // the fewest MFMA tiles per row (ntg * tt), then the most taps per group
         w.packed = true;

@@ -9,6 +9,7 @@ import oracle
 from oracle import backward as ob
 from paper_1508_06904_amd import dss, workloads as wl
 from tests.gpu_helpers import to_device
+from tests.test_gpu_split import _weight_gradient, check
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,17 @@ def test_pool_and_narrow_backward(mid, cout, H, W, act):
     for a, b in zip(list(ws) + list(bs) + [gx], ref[0] + ref[1] + [ref[2]]):
         assert np.abs(b).max() < 2 ** 23
         np.testing.assert_array_equal(a.cpu().numpy().astype(np.float64), b)
+
+
+# 20 and 32 input channels: half a tile of the weight gradient's binary16-part kernel, 1 to 7 taps a group
+@pytest.mark.parametrize("cin", [20, 32])
+@pytest.mark.parametrize("fw", [1, 2, 3, 4, 5, 6, 7])
+def test_weight_gradient_half_tile(cin, fw):
+    import torch
+    w = wl.custom([("conv", cin, 68, 2, fw, "none")], cin, 45, 61, seed=50 + fw, value_kind="normal")
+    G = np.random.default_rng(51).standard_normal((68, 44, 62 - fw)).astype(np.float32)
+    plan = dss.Plan(w.layers, 2, cin)
+    gw, gb, _ = plan.backward(torch.from_numpy(w.x).cuda(), torch.from_numpy(G).cuda(), with_signal_grad=False)
+    torch.cuda.synchronize()
+    got = plan.split_grads(gw, gb)[0][0].cpu().numpy().astype(np.float64)
+    check(got, _weight_gradient(w.x, G, 2, fw), "dW %d channels fw %d" % (cin, fw))
