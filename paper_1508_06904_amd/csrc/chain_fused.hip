@@ -280,7 +280,8 @@ static int64_t fused_regions(const Chain& ch, int TH, int TW, FusedChain* fc) {
 bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, int out_w, double conv_flops,
                 FusedChain* fc) {
     const int L = ch.L();
-    if (L < 1 || L > kMaxFused) return false;
+    // one-dimensional networks have their pools in their convolutions' launches already
+    if (L < 1 || L > kMaxFused || ch.ndim == 1) return false;
     fc->n = L;
     fc->in_c = ch.in_c;
     int launches = 2;            // Stuff and Defrag
@@ -308,7 +309,7 @@ bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, 
     double best = 0.0;
     FusedChain pick = *fc;
     for (int side = 4; side <= 64; side *= 2) {
-        const int TH = ch.ndim == 1 ? 1 : side, TW = ch.ndim == 1 ? side * 4 : side;
+        const int TH = side, TW = side;
         FusedChain t = *fc;
         const int64_t macs = fused_regions(ch, TH, TW, &t);
         if (macs == 0) break;
