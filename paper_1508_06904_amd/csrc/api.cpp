@@ -611,9 +611,10 @@ static dss_status run_layers(dss_plan* p, const Geom& G, int upto, char* const b
             // one-row fragments: the sliding max-pool and Frag in the convolution's
             // epilogue, on spatial tiles of 256 samples stepped by 257 - k; taken
             // when those tiles compute at most 10 % more samples than the layer has
+            // and their halo fits
             const PlanConv pc = mfma_launch_variant(p->convs[j - 1], Fin, lg.Uin_h, lg.Uin_w, 1, 1);
             const int64_t tiles = ((int64_t)c.k_w * lg.U_w + 256 - c.k_w) / (256 - c.k_w + 1);
-            if (pc.impl == CONV_MFMA_F32 && pc.bn <= 64 && 10 * tiles * 256 <= 11 * (int64_t)lg.E_w) {
+            if (pc.impl == CONV_MFMA_F32 && pc.bn <= 64 && 10 * tiles * 256 <= 11 * (int64_t)lg.E_w && mfma_pool_fits(pc)) {
                 void* dst = buf[which ^ 1];
                 const double flops = 2.0 * Fin * (double)lg.E_h * lg.E_w * c.cout * (double)c.cin * c.c_h * c.c_w;
                 const double bytes = (double)Fin * lg.Uin_h * lg.Uin_w * c.cin * 4.0 +

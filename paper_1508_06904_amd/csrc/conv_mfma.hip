@@ -1094,6 +1094,20 @@ int mfma_tile_mode(const PlanConv& pc, int F, int Hin, int Win, int dil_h, int d
     return L.flat ? 1 : 0;
 }
 
+// The halo of a one-row pooled tile (kEpiPool) in the LDS of two workgroups per CU,
+// or false: a filter of more than 244 columns, or of two rows and more, is wider than
+// that and takes the tile that suits it, with the pool in a launch of its own.
+static bool pool_halo(const PlanConv& pc, Tile* t) {
+    *t = Tile{1, kBM, 0, 0};
+    return fit_halo((int64_t)pc.fh * (kBM + pc.fw - 1), pc.impl == CONV_MFMA_BF16,
+                    std::min(device_lds_limit(), (size_t)kMaxLds), t);
+}
+
+bool mfma_pool_fits(const PlanConv& pc) {
+    Tile t;
+    return pool_halo(pc, &t);
+}
+
 template <bool BF16, typename Tout, int WGM, int WGN, int MT, int NT, int EPI>
 static hipError_t run_mfma(const void* in, int F, int Hin, int Win, int dil_h, int dil_w, int pad_h, int pad_w,
                            const PlanConv& pc, void* out, float* part, int pool_k, hipStream_t s) {
@@ -1122,8 +1136,7 @@ static hipError_t run_mfma(const void* in, int F, int Hin, int Win, int dil_h, i
             return hipErrorInvalidValue;
         pool_U = (Wout - pool_k + 1) / pool_k;
         tile_step_w = kBM - pool_k + 1;
-        L.t = Tile{1, kBM, 0, 0};
-        if (!fit_halo((int64_t)pc.fh * (kBM + pc.fw - 1), BF16, kMaxLds, &L.t)) return hipErrorInvalidValue;
+        if (!pool_halo(pc, &L.t)) return hipErrorInvalidValue;
         L.t.lds = std::max(L.t.lds, (size_t)kBM * (32 + 4) * sizeof(float));
         L.flat = 0;
         L.tilesY = 1;

@@ -251,7 +251,9 @@ hipError_t launch_window_scatter_sum(const float* part, int nbs, int count, int 
                                      int64_t first, int64_t plane, float* out, hipStream_t s);
 hipError_t launch_planar_sum(const float* part, int nbs, int h, int w, int C, const float* bias, int act, float* out,
                              hipStream_t s);
-// The binary32 MFMA convolution pc (32- or 64-channel N tile) on fragments of
+// Whether the halo of pc's pooled one-row tile fits beside another workgroup's.
+bool mfma_pool_fits(const PlanConv& pc);
+// The binary32 MFMA convolution pc (32- or 64-channel N tile; mfma_pool_fits) on fragments of
 // one output row, with the sliding max-pool of k samples along the row and
 // Frag_k in its epilogue: out is the pool's fragment tensor [k F][1][U][Cout].
 hipError_t launch_conv_mfma_pool(const float* in, int F, int Hin, int Win, const PlanConv& pc, int pool_k, float* out,
