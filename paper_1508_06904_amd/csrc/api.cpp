@@ -14,7 +14,6 @@
 // workspace, in the channels-last fragment layout [F][h][w][C] (fragment index
 // linearised row-major over (row fragment, column fragment)).
 #include <algorithm>
-#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -81,30 +80,24 @@ static ConvImpl choose_impl(int cin, int cout, int fh, int fw, dss_dtype dt) {
     return CONV_DIRECT;
 }
 
-// The power of two that takes the weights' largest finite magnitude into
-// [2^14, 2^15), within 2^-100 .. 2^100 (1 if there is none), and whether some
-// weight is an infinity or NaN.
-static float weight_scale(const float* w, size_t n, bool* nonfinite) {
-    uint32_t top = 0, any = 0;
+// Whether some weight is an infinity or NaN.
+static bool any_nonfinite(const float* w, size_t n) {
+    uint32_t any = 0;
     for (size_t i = 0; i < n; ++i) {
         uint32_t u;
         std::memcpy(&u, w + i, 4);
-        u &= 0x7fffffffu;
-        any |= (uint32_t)(u >= 0x7f800000u);
-        top = std::max(top, u >= 0x7f800000u ? 0u : u);
+        any |= (uint32_t)((u & 0x7f800000u) == 0x7f800000u);
     }
-    *nonfinite = any != 0;
-    if (top == 0) return 1.f;
-    return std::ldexp(1.f, std::max(-100, std::min(100, 14 - ((int)(top >> 23) - 127))));
+    return any != 0;
 }
 
 // Packs one convolution for the kernel chosen for it and copies it to the current
 // device: out channel n, in channel c, tap t has weight host[n sn + c sc + t], or
 // with flip host[n sn + c sc + taps - 1 - t]; `dev` is the same array on the
-// device (the MFMA layouts are packed there, on the null stream).  scale and
-// nonfinite are weight_scale()'s (binary32).  bias [cout] on the host or NULL.
+// device (the MFMA layouts are packed there, on the null stream).  bias [cout] on
+// the host or NULL.
 static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const float* host, const WeightView& dev,
-                              float scale, const float* bias_in, dss_dtype dtype, PlanConv& pc) {
+                              const float* bias_in, dss_dtype dtype, PlanConv& pc) {
     pc.cin = cin;
     pc.cout = cout;
     pc.fh = fh;
@@ -138,9 +131,9 @@ static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const 
         pc.cin_pad = (cin + 31) / 32 * 32;
         pc.cout_pad = (cout + pc.bn - 1) / pc.bn * pc.bn;
         pc.wv = dev;
-        pc.w_unscale = bf16 ? 1.f : 1.f / scale;
         e = hipMalloc(&pc.w, mfma_packed_bytes(pc));
-        if (e == hipSuccess) e = launch_pack_mfma(pc, bf16 ? 1.f : scale, nullptr);
+        if (e == hipSuccess && !bf16) e = hipMalloc((void**)&pc.w_scale, sizeof(float) * pc.cout_pad);
+        if (e == hipSuccess) e = launch_pack_mfma(pc, nullptr);
     }
     std::vector<float> bias(pc.cout_pad, 0.f);
     for (int o = 0; o < cout; ++o) bias[o] = bias_in ? bias_in[o] : 0.f;
@@ -287,9 +280,11 @@ static void free_plan_memory(dss_plan* p) {
             if (c.w) (void)hipFree(c.w);
             if (c.b) (void)hipFree(c.b);
             if (c.w2) (void)hipFree(c.w2);
+            if (c.w_scale) (void)hipFree(c.w_scale);
             c.w = nullptr;
             c.b = nullptr;
             c.w2 = nullptr;
+            c.w_scale = nullptr;
         }
     for (float* w : p->wraw)
         if (w) (void)hipFree(w);
@@ -397,15 +392,13 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
                 break;
             }
         }
-        bool nonfinite = false;
-        const float scale = dtype == DSS_F32 ? weight_scale(d.weight, n, &nonfinite) : 1.f;
+        const bool nonfinite = dtype == DSS_F32 && any_nonfinite(d.weight, n);
         const WeightView fwd{p->wraw[j], (int64_t)c.cin * taps, taps, 0, nonfinite};
-        s = upload_conv(c.cin, c.cout, c.c_h, c.c_w, c.act, d.weight, fwd, scale, d.bias, dtype, p->convs[j]);
+        s = upload_conv(c.cin, c.cout, c.c_h, c.c_w, c.act, d.weight, fwd, d.bias, dtype, p->convs[j]);
         if (s == DSS_OK && dtype == DSS_F32) {
             // input gradient: w'[i][o][t_h][t_w] = w[o][i][fh-1-t_h][fw-1-t_w]
             const WeightView bwd{p->wraw[j], taps, (int64_t)c.cin * taps, 1, nonfinite};
-            s = upload_conv(c.cout, c.cin, c.c_h, c.c_w, DSS_ACT_NONE, d.weight, bwd, scale, nullptr, dtype,
-                            p->bconvs[j]);
+            s = upload_conv(c.cout, c.cin, c.c_h, c.c_w, DSS_ACT_NONE, d.weight, bwd, nullptr, dtype, p->bconvs[j]);
         }
     }
     if (s == DSS_OK) s = setup_fusions(p, layers);

@@ -36,9 +36,9 @@
 //   1.5e-7, 9216 1.22e-6 -> 3.4e-7.  (Three bfloat16 parts and six products need
 //   no scale and reach 3.3e-7 at K = 9216, at twice the matrix cycles.)
 //   S is chosen per staged sample and 32-channel chunk, the power of two that
-//   takes the sample's largest magnitude into [2^14, 2^15) (a layer-wide one for
-//   the weights): it depends on nothing but the sample itself, so every fashion,
-//   tile shape and batch gives the same bits.  A channel keeps all its bits down
+//   takes the sample's largest magnitude into [2^14, 2^15) (for the weights one per
+//   output channel, which the epilogue takes out again): it depends on nothing but
+//   the sample itself, so every fashion, tile shape and batch gives the same bits.  A channel keeps all its bits down
 //   to 2^-17 of its sample's largest and an absolute 2^-40 of that below.  An
 //   infinity leaves no finite parts: outputs that a staged infinity (or a
 //   non-finite weight) made non-finite are summed again in plain binary32
@@ -138,8 +138,10 @@ __device__ __forceinline__ void split_f16(const float (&v)[8], float scale, u32x
     lo = __builtin_bit_cast(u32x4, l);
 }
 
-// Power of two that takes a largest magnitude with these bits into [2^14, 2^15):
-// 2^110 for magnitudes below 2^-96 (zero among them).
+// Power of two S that takes a largest magnitude with these bits into [2^14, 2^15):
+// 2^110 for magnitudes below 2^-96 (zero among them).  The bits of 2^-14 / S are
+// kUnscale minus S's.
+constexpr uint32_t kUnscale = 240u << 23;
 __device__ __forceinline__ uint32_t scale_bits(uint32_t max_bits) {
     return min((268u << 23) - (max_bits & 0x7f800000u), 237u << 23);
 }
@@ -168,7 +170,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     int64_t part_stride,                // kEpiProj: floats per channel group of part
     int tile_step_w,                    // columns between neighbouring tiles (TW, or TW - k + 1 with kEpiPool)
     int pool_k, int pool_U,             // kEpiPool: pool size along the row, pooled samples per fragment
-    WeightView wv, float w_unscale) {   // binary32: the weights as given, and 2^-s of their scale
+    WeightView wv,                      // binary32: the weights as given
+    const float* __restrict__ w_scale) {   // binary32: [Cout_pad], e_n of channel n's weights (kTop / S)
     using Cfg = MfmaCfg<WGM, WGN, MT, NT>;
     constexpr int THREADS = kThreads;
     constexpr int PITCH = BF16 ? kPitchBf16 : kPitchF32;
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     *reinterpret_cast<u32x4*>(dst) = hi;
                     *reinterpret_cast<u32x4*>(dst + 64) = lo;
                     if (st_q == 0)
-                        *reinterpret_cast<float*>(dst + kScaleAt) = __uint_as_float((254u << 23) - sb) * w_unscale;
+                        *reinterpret_cast<float*>(dst + kScaleAt) = __uint_as_float(kUnscale - sb);
                 }
             }
         };
@@ -603,6 +606,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         o = f_off + (size_t)y * Wout + x;
         return y < Hout && x < Wout;
     };
+    // binary32: the powers of two of the channels' weights
+    if constexpr (!BF16) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const floatx4 e = *reinterpret_cast<const floatx4*>(w_scale + n_base + tile_channel(false, nt, le_grp * 4));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] *= e;
+        }
+    }
     // binary32: outputs that are not finite although their binary32 sum may be, or
     // may be another infinity.  With an infinity or NaN among the workgroup's
     // inputs, or in the weights, bit k = (mt NT + nt) 4 + v of `bad` marks the
@@ -874,14 +886,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         epilogue(std::integral_constant<int, 0>{});
 }
 
+// e_n, the power of two at or below the largest finite magnitude of channel n's
+// weights (at least 2^-112, so that the weights' scale 2^14 / e_n is finite; 0 for
+// a channel without any).  One workgroup per channel.
+__global__ __launch_bounds__(256) void weight_scale_kernel(WeightView wv, int cout, int cin, int taps,
+                                                          float* __restrict__ w_scale) {
+    __shared__ uint32_t top;
+    const int n = blockIdx.x;
+    if (threadIdx.x == 0) top = 0u;
+    __syncthreads();
+    uint32_t m = 0;
+    const int64_t count = n < cout ? (int64_t)cin * taps : 0;
+    for (int64_t i = threadIdx.x; i < count; i += 256) {
+        const int64_t c = i / taps;
+        const uint32_t b = __float_as_uint(wv.w[(int64_t)n * wv.sn + c * wv.sc + (i - c * taps)]) & 0x7fffffffu;
+        m = max(m, b < 0x7f800000u ? b : 0u);
+    }
+    atomicMax(&top, m);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        w_scale[n] = top == 0u ? 0.f : __uint_as_float(max(top & 0x7f800000u, 15u << 23));
+}
+
 // Packs a convolution's weights into the order the kernel's lanes load: slices
 // [N block of rows][chunk][th][tw] of rows / 16 tiles, each 64 lanes x 16 bytes per
 // part (lane 16 g + r: channels 8 g .. 8 g + 7 of row r).  One thread per lane of a
 // tile; rows and channels past the layer's are zero.
 template <bool BF16>
 __global__ __launch_bounds__(256) void pack_weights_kernel(WeightView wv, int cout, int cin, int taps, int rows,
-                                                          int nchunks, float scale, u32x4* __restrict__ dst,
-                                                          int64_t nthreads) {
+                                                          int nchunks, const float* __restrict__ w_scale,
+                                                          u32x4* __restrict__ dst, int64_t nthreads) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= nthreads) return;
     const int lane = (int)(idx & 63), tiles = rows >> 4;
@@ -908,7 +942,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(WeightView wv, int co
         dst[tile_index * 64 + lane] = __builtin_bit_cast(u32x4, h);
     } else {
         u32x4 hi, lo;
-        split_f16(v, scale, hi, lo);
+        split_f16(v, n < cout && w_scale[n] > 0.f ? 16384.f / w_scale[n] : 0.f, hi, lo);
         dst[tile_index * 128 + lane] = hi;
         dst[tile_index * 128 + 64 + lane] = lo;
     }
@@ -922,16 +956,18 @@ size_t mfma_packed_bytes(const PlanConv& pc) {
     return (size_t)(pc.cout_pad / 16) * (pc.cin_pad / kCC) * pc.fh * pc.fw * tile_bytes(pc.impl == CONV_MFMA_BF16);
 }
 
-hipError_t launch_pack_mfma(const PlanConv& pc, float scale, hipStream_t s) {
+hipError_t launch_pack_mfma(const PlanConv& pc, hipStream_t s) {
     const bool bf16 = pc.impl == CONV_MFMA_BF16;
     const int64_t n = (int64_t)(mfma_packed_bytes(pc) / tile_bytes(bf16)) * 64;
     const dim3 grid((unsigned)ceil_div64(n, 256));
+    if (!bf16)
+        weight_scale_kernel<<<dim3((unsigned)pc.cout_pad), 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.w_scale);
     if (bf16)
         pack_weights_kernel<true><<<grid, 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.pack_rows,
-                                                       pc.cin_pad / kCC, scale, (u32x4*)pc.w, n);
+                                                       pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w, n);
     else
         pack_weights_kernel<false><<<grid, 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.pack_rows,
-                                                        pc.cin_pad / kCC, scale, (u32x4*)pc.w, n);
+                                                        pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w, n);
     return hipGetLastError();
 }
 
@@ -1157,13 +1193,13 @@ static hipError_t run_mfma(const void* in, int F, int Hin, int Win, int dil_h, i
         kern<<<dim3((unsigned)L.nblocks), kThreads, L.t.lds, s>>>(
             (const char*)in, 1, flat_len, pc.cin, (const char*)pc.w, pc.pack_rows, pc.b, pc.fh, pc.fw, pc.cout, pc.act, nchunks,
             (Tout*)out, Hout, Wout, 1, L.t.TW, 1, L.tilesX, nbs, L.t.dbl, Hin, Win, 1, 1, 0, 0, pc.w2, part,
-            part_stride, L.t.TW, 0, 0, pc.wv, pc.w_unscale);
+            part_stride, L.t.TW, 0, 0, pc.wv, pc.w_scale);
         return hipGetLastError();
     }
     kern<<<dim3((unsigned)L.nblocks), kThreads, L.t.lds, s>>>(
         (const char*)in, Hin, Win, pc.cin, (const char*)pc.w, pc.pack_rows, pc.b, pc.fh, pc.fw, pc.cout, pc.act, nchunks,
         (Tout*)out, Hout, Wout, L.t.TH, L.t.TW, L.tilesY, L.tilesX, nbs, L.t.dbl, 0, 0, dil_h, dil_w, pad_h, pad_w,
-        pc.w2, part, part_stride, tile_step_w, pool_k, pool_U, pc.wv, pc.w_unscale);
+        pc.w2, part, part_stride, tile_step_w, pool_k, pool_U, pc.wv, pc.w_scale);
     return hipGetLastError();
 }
 

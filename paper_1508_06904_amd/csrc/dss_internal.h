@@ -100,9 +100,10 @@ struct PlanConv {
     int pack_rows = 0;          // MFMA kernels: output channels per packed weight slice (the plan's bn; a
                                 // launch with a narrower N tile reads parts of the slices)
     // binary32 MFMA kernel: the weights as given (its non-finite outputs are summed
-    // again from them) and 2^-s of the power of two that their binary16 parts carry
+    // again from them) and, device [cout_pad], the power of two e_n that every output
+    // channel's weights were divided by for their binary16 parts
     WeightView wv;
-    float w_unscale = 1.f;
+    float* w_scale = nullptr;
     // MFMA convolution followed by a folded 1x1 projection: its weights as
     // [cout_pad][4] binary32 (zero padded), device
     float* w2 = nullptr;
@@ -302,8 +303,8 @@ hipError_t allow_dynamic_lds(const void* kern, size_t bytes);
 bool mfma_supports(int fh, int fw);
 int mfma_pick_bn(int cout);
 size_t mfma_packed_bytes(const PlanConv& pc);
-// Packs pc.wv (times scale, binary32) into pc.w on the device.
-hipError_t launch_pack_mfma(const PlanConv& pc, float scale, hipStream_t s);
+// Packs pc.wv into pc.w (and pc.w_scale, binary32) on the device.
+hipError_t launch_pack_mfma(const PlanConv& pc, hipStream_t s);
 
 uint16_t host_f32_to_bf16(float f);
 
