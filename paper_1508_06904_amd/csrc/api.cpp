@@ -80,17 +80,6 @@ static ConvImpl choose_impl(int cin, int cout, int fh, int fw, dss_dtype dt) {
     return CONV_DIRECT;
 }
 
-// Whether some weight is an infinity or NaN.
-static bool any_nonfinite(const float* w, size_t n) {
-    uint32_t any = 0;
-    for (size_t i = 0; i < n; ++i) {
-        uint32_t u;
-        std::memcpy(&u, w + i, 4);
-        any |= (uint32_t)((u & 0x7f800000u) == 0x7f800000u);
-    }
-    return any != 0;
-}
-
 // Packs one convolution for the kernel chosen for it and copies it to the current
 // device: out channel n, in channel c, tap t has weight host[n sn + c sc + t], or
 // with flip host[n sn + c sc + taps - 1 - t]; `dev` is the same array on the
@@ -132,7 +121,8 @@ static dss_status upload_conv(int cin, int cout, int fh, int fw, int act, const 
         pc.cout_pad = (cout + pc.bn - 1) / pc.bn * pc.bn;
         pc.wv = dev;
         e = hipMalloc(&pc.w, mfma_packed_bytes(pc));
-        if (e == hipSuccess && !bf16) e = hipMalloc((void**)&pc.w_scale, sizeof(float) * pc.cout_pad);
+        if (e == hipSuccess && !bf16) e = hipMalloc((void**)&pc.w_scale, 2 * sizeof(float) * pc.cout_pad);
+        if (e == hipSuccess && !bf16) e = hipMalloc((void**)&pc.w32, mfma_packed_bytes(pc));
         if (e == hipSuccess) e = launch_pack_mfma(pc, nullptr);
     }
     std::vector<float> bias(pc.cout_pad, 0.f);
@@ -281,10 +271,12 @@ static void free_plan_memory(dss_plan* p) {
             if (c.b) (void)hipFree(c.b);
             if (c.w2) (void)hipFree(c.w2);
             if (c.w_scale) (void)hipFree(c.w_scale);
+            if (c.w32) (void)hipFree(c.w32);
             c.w = nullptr;
             c.b = nullptr;
             c.w2 = nullptr;
             c.w_scale = nullptr;
+            c.w32 = nullptr;
         }
     for (float* w : p->wraw)
         if (w) (void)hipFree(w);
@@ -392,12 +384,11 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
                 break;
             }
         }
-        const bool nonfinite = dtype == DSS_F32 && any_nonfinite(d.weight, n);
-        const WeightView fwd{p->wraw[j], (int64_t)c.cin * taps, taps, 0, nonfinite};
+        const WeightView fwd{p->wraw[j], (int64_t)c.cin * taps, taps, 0};
         s = upload_conv(c.cin, c.cout, c.c_h, c.c_w, c.act, d.weight, fwd, d.bias, dtype, p->convs[j]);
         if (s == DSS_OK && dtype == DSS_F32) {
             // input gradient: w'[i][o][t_h][t_w] = w[o][i][fh-1-t_h][fw-1-t_w]
-            const WeightView bwd{p->wraw[j], taps, (int64_t)c.cin * taps, 1, nonfinite};
+            const WeightView bwd{p->wraw[j], taps, (int64_t)c.cin * taps, 1};
             s = upload_conv(c.cout, c.cin, c.c_h, c.c_w, DSS_ACT_NONE, d.weight, bwd, nullptr, dtype, p->bconvs[j]);
         }
     }
@@ -407,11 +398,13 @@ extern "C" dss_status dss_plan_create(const dss_layer* layers, int32_t n_layers,
         e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) s = hip_fail(e, "packing weights");
     }
-    if (s == DSS_OK && dtype == DSS_BF16)   // only the binary32 kernel reads them again
-        for (float*& w : p->wraw) {
+    if (s == DSS_OK) {
+        for (float* w : p->wraw)
             if (w) (void)hipFree(w);
-            w = nullptr;
-        }
+        p->wraw.clear();
+        for (auto* list : {&p->convs, &p->bconvs})
+            for (PlanConv& c : *list) c.wv = WeightView{};
+    }
     if (s != DSS_OK) {
         free_plan_memory(p);
         delete p;

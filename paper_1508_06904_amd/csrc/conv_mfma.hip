@@ -38,11 +38,19 @@
 //   S is chosen per staged sample and 32-channel chunk, the power of two that
 //   takes the sample's largest magnitude into [2^14, 2^15) (for the weights one per
 //   output channel, which the epilogue takes out again): it depends on nothing but
-//   the sample itself, so every fashion, tile shape and batch gives the same bits.  A channel keeps all its bits down
-//   to 2^-17 of its sample's largest and an absolute 2^-40 of that below.  An
-//   infinity leaves no finite parts: outputs that a staged infinity (or a
-//   non-finite weight) made non-finite are summed again in plain binary32
-//   (fix_nonfinite).
+//   the sample itself, so every fashion, tile shape and batch gives the same bits.
+//   A value keeps all its bits down to 2^-17 of its sample's (filter's) largest and
+//   an absolute 2^-40 of that below.  That is lost only where the large values meet
+//   small or no weights, so every output is certified: the sum of what its samples'
+//   parts left out (kept beside the sample in LDS) and of what its filter's did,
+//   each times the largest value it can have met, must stay below sqrt(K) 2^-24 of
+//   the output's own magnitude, what the K additions themselves lose in binary32.  Outputs that fail, and those that are not finite (an
+//   infinity leaves no finite parts), are summed again with the binary32 matrix
+//   instruction from the inputs and weights as they are.  The certificate is a
+//   property of the output's window alone too.  On N(0,1) data a few outputs
+//   of a layer fail, if any (the certificate costs 0.1 to 4 % of a call, most on layers
+//   of few taps: HD frame 42.1 -> 42.6 ms, twelve layers of 128 maps 0.862 -> 0.895);
+//   on channels that differ by 2^20 and more against their weights all do.
 //
 // Spatial tiles may read a virtual zero border of pad_h x pad_w samples around
 // every fragment (the input gradient of the backward pass); small fragments can
@@ -55,7 +63,7 @@
 // Epilogue: + bias, activation, masked 16-byte stores (edge tiles, padded
 // channels) in the channels-last output layout.
 #include <algorithm>
-
+#include <cmath>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -80,8 +88,11 @@ constexpr int kBM = 256;            // output samples per workgroup
 // of the others.  With a pitch of 16-byte units = 2 (mod 4) (160 bytes) those 16
 // units fall in 16 different bank groups, with 64 bytes the rotation does it.
 constexpr int kPitchBf16 = 64, kPitchF32 = 160;
-constexpr int kScaleAt = 128;       // binary32: byte offset of a sample's scale
-constexpr int kLdsHead = 128;       // bytes before the halo (the non-finite flag)
+constexpr int kScaleAt = 128;       // binary32: byte offset of 2^-14 / S of a sample's chunk
+constexpr int kLossAt = 136;        // ... and of what its parts left out (times that, summed over the chunks
+                                    // so far) and of the largest 2^-14 / S of the chunks
+constexpr int kBadAt = 144;         // ... and the outputs of this sample that failed their certificate
+constexpr int kLdsHead = 128;       // bytes before the halo (binary32: both of the above over the workgroup)
 constexpr int kMaxLds = 78 * 1024;  // two workgroups per CU (160 KB of LDS)
 constexpr int kMaxLds1 = 156 * 1024;  // one workgroup per CU (filters too wide for two)
 constexpr int kXcds = 8;            // accelerator complex dies of an MI355X
@@ -138,6 +149,17 @@ __device__ __forceinline__ void split_f16(const float (&v)[8], float scale, u32x
     lo = __builtin_bit_cast(u32x4, l);
 }
 
+// What the parts leave out of the values that may lose bits, in the same unit.
+__device__ __forceinline__ float split_loss(const float (&v)[8], float scale) {
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float y = v[i] * scale, r = y - (float)(_Float16)y;
+        sum += fabsf(y) < 0.25f ? fabsf(r - (float)(_Float16)r) : 0.f;
+    }
+    return sum;
+}
+
 // Power of two S that takes a largest magnitude with these bits into [2^14, 2^15):
 // 2^110 for magnitudes below 2^-96 (zero among them).  The bits of 2^-14 / S are
 // kUnscale minus S's.
@@ -170,8 +192,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     int64_t part_stride,                // kEpiProj: floats per channel group of part
     int tile_step_w,                    // columns between neighbouring tiles (TW, or TW - k + 1 with kEpiPool)
     int pool_k, int pool_U,             // kEpiPool: pool size along the row, pooled samples per fragment
-    WeightView wv,                      // binary32: the weights as given
-    const float* __restrict__ w_scale) {   // binary32: [Cout_pad], e_n of channel n's weights (kTop / S)
+    const float* __restrict__ w32,      // binary32: the weights as they are, in the packed tiles' order
+    float cert,                         // binary32: how often an output must exceed what its sum may have lost
+    const float* __restrict__ w_scale) {   // binary32: [Cout_pad][2], e_n and what the parts of the weights leave out
     using Cfg = MfmaCfg<WGM, WGN, MT, NT>;
     constexpr int THREADS = kThreads;
     constexpr int PITCH = BF16 ? kPitchBf16 : kPitchF32;
@@ -424,9 +447,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         // Stages chunk cn: rounds of 64 samples, kRounds rounds' loads in flight
         // together.  The four threads of a sample find its largest magnitude, hence
         // its scale, by two exchanges within their quad.
-        constexpr int kRounds = MT * NT == 16 ? 3 : 4;
-        uint32_t* const flag = reinterpret_cast<uint32_t*>(lds);
-        auto stage_split = [&](int cn) {
+        constexpr int kRounds = MT * NT == 32 ? 4 : MT * NT == 16 && EPI != kEpiPool ? 3 : 2;   // (registers)
+        float* const head = reinterpret_cast<float*>(lds);
+        auto stage_split = [&](int cn) __attribute__((always_inline)) {
             // computed here each time: held through the K loop, these would take
             // registers from the accumulators
             int tid_s = tid;
@@ -435,42 +458,85 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const char* src_c = in_f + (size_t)cn * (kCC * ES) + st_q * 32;
             const int c0 = cn * kCC + st_q * 8;
             int dy = (tid_s >> 2) / HW, dx = (tid_s >> 2) - dy * HW;
+            // channels c0 .. c0 + 7 of halo sample p
+            auto load = [&](int p, int sy, int sx, float (&q)[8]) {
+                const int yy = hy0 + sy, xx = hx0 + sx;
+                const bool ok = p < halo_px && (unsigned)yy < (unsigned)lim_h && (unsigned)xx < (unsigned)lim_w &&
+                                c0 < Cin;
+                const char* src = src_c + (size_t)yy * row_step + (size_t)xx * col_step;
+                const floatx4 a = *reinterpret_cast<const floatx4*>(ok ? src : zero);
+                const floatx4 b = *reinterpret_cast<const floatx4*>(ok && c0 + 4 < Cin ? src + 16 : zero);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    q[e] = a[e];
+                    q[4 + e] = b[e];
+                }
+            };
+            auto top_bits = [](const float (&q)[8]) {
+                // (v_max3_f32 takes magnitudes for nothing and passes NaN by)
+                float top = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2)
+                    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(q[e]), "v"(q[e + 1]));
+                uint32_t mb = __float_as_uint(top);
+                mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0xB1, 0xf, 0xf, true));   // lane ^ 1
+                return max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0x4E, 0xf, 0xf, true));  // lane ^ 2
+            };
+            uint32_t un_max = 0;
             for (int p0 = tid_s >> 2; p0 < halo_px; p0 += 64 * kRounds) {
                 float v[kRounds][8];
+                uint32_t lossy = 0;
 #pragma unroll
                 for (int r = 0; r < kRounds; ++r) {
-                    const int yy = hy0 + dy, xx = hx0 + dx;
-                    const bool ok = p0 + 64 * r < halo_px && (unsigned)yy < (unsigned)lim_h &&
-                                    (unsigned)xx < (unsigned)lim_w && c0 < Cin;
-                    const char* src = src_c + (size_t)yy * row_step + (size_t)xx * col_step;
-                    const floatx4 a = *reinterpret_cast<const floatx4*>(ok ? src : zero);
-                    const floatx4 b = *reinterpret_cast<const floatx4*>(ok && c0 + 4 < Cin ? src + 16 : zero);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[r][e] = a[e];
-                        v[r][4 + e] = b[e];
-                    }
+                    load(p0 + 64 * r, dy, dx, v[r]);
                     advance(dy, dx);
                 }
 #pragma unroll
                 for (int r = 0; r < kRounds; ++r) {
                     if (p0 + 64 * r >= halo_px) break;
-                    uint32_t mb = 0;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) mb = max(mb, __float_as_uint(v[r][e]) & 0x7fffffffu);
-                    mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0xB1, 0xf, 0xf, true));   // lane ^ 1
-                    mb = max(mb, (uint32_t)__builtin_amdgcn_mov_dpp((int)mb, 0x4E, 0xf, 0xf, true));   // lane ^ 2
-                    const uint32_t sb = scale_bits(mb);
-                    if (mb >= 0x7f800000u) *flag = 1u;   // an infinity or a NaN in this sample
+                    const uint32_t mb = top_bits(v[r]), sb = scale_bits(mb);
+                    const uint32_t un = kUnscale - sb;
                     u32x4 hi, lo;
                     split_f16(v[r], __uint_as_float(sb), hi, lo);
                     char* dst = halo0 + (p0 + 64 * r) * PITCH + st_q * 16;
                     *reinterpret_cast<u32x4*>(dst) = hi;
                     *reinterpret_cast<u32x4*>(dst + 64) = lo;
-                    if (st_q == 0)
-                        *reinterpret_cast<float*>(dst + kScaleAt) = __uint_as_float(kUnscale - sb);
+                    if (st_q == 0) {
+                        *reinterpret_cast<uint32_t*>(dst + kScaleAt) = un;
+                        const uint32_t x = mb ? un : 0u;      // (a sample of zeros loses nothing)
+                        uint32_t* const rec = reinterpret_cast<uint32_t*>(dst + kLossAt);
+                        if (cn == 0) *reinterpret_cast<uint2*>(rec) = make_uint2(0u, x);
+                        else atomicMax(rec + 1, x);
+                    }
+                    un_max = max(un_max, un);
+                    // a value other than 0 below 2^-2 / S may lose bits (twice its magnitude less 1: 0 comes last)
+                    uint32_t mn = ~0u;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) mn = min(mn, (__float_as_uint(v[r][e]) << 1) - 1u);
+                    lossy |= (uint32_t)(mn < (((252u << 23) - sb) << 1) - 1u);
+                }
+                if (__any(lossy != 0)) {
+#pragma unroll
+                    for (int r = 0; r < kRounds; ++r) {
+                        if (p0 + 64 * r >= halo_px) break;
+                        const uint32_t mb = top_bits(v[r]), sb = scale_bits(mb);
+                        float lost = split_loss(v[r], __uint_as_float(sb)) * __uint_as_float(kUnscale - sb);
+                        if (mb < (31u << 23) && mb != 0) lost = __builtin_inff();   // S could not follow
+                        lost += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(lost), 0xB1, 0xf, 0xf, true));
+                        lost += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(lost), 0x4E, 0xf, 0xf, true));
+                        if (st_q == 0 && lost > 0.f) {
+                            *reinterpret_cast<float*>(halo0 + (p0 + 64 * r) * PITCH + kLossAt) += lost;
+                            atomicAdd(&head[0], lost);
+                        }
+                    }
                 }
             }
+            // over the wave: within rows of 16 lanes, then row by row into lane 63
+            un_max = max(un_max, (uint32_t)__builtin_amdgcn_mov_dpp((int)un_max, 0x124, 0xf, 0xf, true));   // rotated by 4
+            un_max = max(un_max, (uint32_t)__builtin_amdgcn_mov_dpp((int)un_max, 0x128, 0xf, 0xf, true));   // ... by 8
+            un_max = max(un_max, (uint32_t)__builtin_amdgcn_mov_dpp((int)un_max, 0x142, 0xf, 0xf, true));   // row before
+            un_max = max(un_max, (uint32_t)__builtin_amdgcn_mov_dpp((int)un_max, 0x143, 0xf, 0xf, true));   // two rows
+            if ((tid_s & 63) == 63) atomicMax(reinterpret_cast<uint32_t*>(head) + 1, un_max);
         };
         // One step.  A tile's sum over the step's 32 channels starts from zero, the
         // smallest products first, and is added unscaled to its accumulator.  Two
@@ -551,7 +617,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             add(MT * NT / 2 - 1, 1);
         };
         u32x4 bA[NT][2], bB[NT][2];
-        if (tid == 0) *flag = 0u;
+        if (tid < 2) head[tid] = 0.f;
         __syncthreads();
         load_b(0, bA);
         stage_split(0);
@@ -606,58 +672,176 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         o = f_off + (size_t)y * Wout + x;
         return y < Hout && x < Wout;
     };
-    // binary32: the powers of two of the channels' weights
+    // byte offset of the lane's sample of MFMA tile mt inside the halo, as tile_off() and lane_off
+    auto sample_off = [&](int mt, int ln) {
+        return tile_off(mt) + (TW == 8 ? (((ln & 15) >> 3) << row_lg) * HW + (ln & 7) : ln & 15) * PITCH;
+    };
+    // where the lane keeps which of its outputs of tile row mt have failed: beside its own sample, 16 bits a lane
+    auto bad_mask = [&](int mt, int ln) {
+        return reinterpret_cast<uint16_t*>(halo0 + sample_off(mt, ln) + kBadAt + (wn * 4 + (ln >> 4)) * 2);
+    };
+    // The sums of tiles (mt, nt) .. (mt, nt + N - 1) from the inputs and weights as they are, in
+    // global memory, U steps' operands loaded together: K slot g of matrix instruction j holds
+    // channel 8 g + j of the chunk.
+    auto exact_sums = [&](int mt, int nt, int ln, auto& sum, auto u_c) __attribute__((always_inline)) {
+        constexpr int N = sizeof(sum) / sizeof(floatx4), U = decltype(u_c)::value;
+        const int m = (wm * MT + mt) * 16 + (ln & 15);
+        const int y0 = flat_w ? 0 : hy0 + tile_dy(m), x0 = flat_w ? tx0 + m : hx0 + (m & (TW - 1));
+        const float* ws = w32 + ln * 8 +
+                          ((size_t)(n_base / pack_rows) * steps * (pack_rows >> 4) + ((n_base % pack_rows) >> 4) + nt) * 512;
+#pragma unroll
+        for (int n = 0; n < N; ++n) sum[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+        int a = 0, b = 0, c0 = (ln >> 4) * 8;
+#pragma nounroll
+        for (int st = 0; st < steps; st += U) {
+            floatx4 x[U][2], w[U][N][2];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int yy = flat_w ? 0 : y0 + a, xx = flat_w ? x0 + a * flat_w + b : x0 + b;
+                const bool on = st + u < steps;              // past the last step: zeros
+                const bool in_range = on && (unsigned)yy < (unsigned)lim_h && (unsigned)xx < (unsigned)lim_w && c0 < Cin;
+                const char* src = in_f + (size_t)yy * row_step + (size_t)xx * col_step + (size_t)c0 * ES;
+                x[u][0] = *reinterpret_cast<const floatx4*>(in_range ? src : zero);
+                x[u][1] = *reinterpret_cast<const floatx4*>(in_range && c0 + 4 < Cin ? src + 16 : zero);
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        w[u][n][k] = *reinterpret_cast<const floatx4*>(on ? (const char*)(ws + n * 512 + k * 4) : zero);
+                ws += (size_t)(pack_rows >> 4) * 512;
+                if (++b == fw) {
+                    b = 0;
+                    if (++a == fh) {
+                        a = 0;
+                        c0 += kCC;
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int n = 0; n < N; ++n)
+                        sum[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][n][j >> 2][j & 3], x[u][j >> 2][j & 3], sum[n], 0, 0,
+                                                                      0);
+        }
+    };
+    // the lane number again: a value of its own, so that nothing derived from it is shared with other places and
+    // kept in registers between them
+    auto lane_again = [] {
+        int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(ln));
+        return ln;
+    };
+    // e_n and the loss of the weights of the lane's channels of tile nt
+    auto load_scale = [&](const float* sc, int nt, int ln, floatx4& e, floatx4& wl) {
+        const size_t c = n_base + tile_channel(false, nt, (ln >> 4) * 4);
+        const floatx4 s0 = *reinterpret_cast<const floatx4*>(sc + 2 * c), s1 = *reinterpret_cast<const floatx4*>(sc + 2 * c + 4);
+        e = floatx4{s0[0], s0[2], s1[0], s1[2]};
+        wl = floatx4{s0[1], s0[3], s1[1], s1[3]};
+    };
+    bool redo = false;                  // binary32, wave-uniform: some output has failed
+    // binary32: the powers of two of the channels' weights, and the certificate.  In
+    // units of e_n an output's sums are off by at most 2^15 (L + X w_n): L the loss of the
+    // window's samples (times 2^-14 / S; weights are below 2 e_n), X the largest
+    // 2^-14 / S among them (a sample is below 2^15 / S, its parts' loss in units of
+    // 1 / S) and w_n the loss of the channel's weights (in units of 2^-14 e_n).  First
+    // with the workgroup's L and X for all outputs, then, hardly ever, with the
+    // window's own.
     if constexpr (!BF16) {
+        const float kCert = 32768.f * cert;              // 2^15 times the certificate's factor
+        const float* const head = reinterpret_cast<const float*>(lds);
+        const float l_all = 2.f * head[0], x_all = 2.f * head[1];
+        uint32_t worst = 0;                              // of |sum| - threshold: negative, infinite and NaN come last
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const floatx4 e = *reinterpret_cast<const floatx4*>(w_scale + n_base + tile_channel(false, nt, le_grp * 4));
+            floatx4 e, wl, thr;
+            load_scale(w_scale, nt, lane_e, e, wl);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] *= e;
-        }
-    }
-    // binary32: outputs that are not finite although their binary32 sum may be, or
-    // may be another infinity.  With an infinity or NaN among the workgroup's
-    // inputs, or in the weights, bit k = (mt NT + nt) 4 + v of `bad` marks the
-    // lane's non-finite sums; the epilogue then replaces what came of them by the
-    // plain binary32 sum, one output at a time.  Hardly ever reached.
-    constexpr int NBAD = MT * NT * 4 / 32;
-    uint32_t bad[NBAD] = {};
-    if constexpr (!BF16) {
-        if (wv.nonfinite || *reinterpret_cast<const uint32_t*>(lds)) {
+            for (int v = 0; v < 4; ++v) thr[v] = kCert * (l_all + x_all * wl[v]) * e[v];
 #pragma unroll
-            for (int k = 0; k < MT * NT * 4; ++k)
-                bad[k >> 5] |= (fabsf(acc[k / (NT * 4)][(k >> 2) % NT][k & 3]) < __builtin_inff() ? 0u : 1u) << (k & 31);
-        }
-    }
-    // output channel n of tile position m as a plain binary32 sum (one that has become NaN stays so and ends)
-    auto plain_sum = [&](int m, int n) -> float {
-        float sum = 0.f;
-        for (int t = 0; t < taps; ++t) {
-            const int a = t / fw, b = t - a * fw;
-            const int yy = flat_w ? 0 : hy0 + tile_dy(m) + a;
-            const int xx = flat_w ? tx0 + m + a * flat_w + b : hx0 + (m & (TW - 1)) + b;
-            if ((unsigned)yy >= (unsigned)lim_h || (unsigned)xx >= (unsigned)lim_w) continue;
-            const float* xs = reinterpret_cast<const float*>(in_f + (size_t)yy * row_step + (size_t)xx * col_step);
-            const float* ws = wv.w + (int64_t)n * wv.sn + (wv.flip ? taps - 1 - t : t);
-#pragma nounroll
-            for (int c = 0; c < Cin && sum == sum; ++c) sum = fmaf(xs[c], ws[(int64_t)c * wv.sc], sum);
-        }
-        return sum;
-    };
-    // fn(m, n) for the lane's marked outputs: tile position, channel within the wave's
-    auto for_each_bad = [&](auto&& fn) {
-#pragma nounroll
-        for (int w = 0; w < NBAD; ++w) {
-            uint32_t bits = bad[0];
+            for (int mt = 0; mt < MT; ++mt) {
+                acc[mt][nt] *= e;
 #pragma unroll
-            for (int i = 1; i < NBAD; ++i) bits = w == i ? bad[i] : bits;
-#pragma nounroll
-            for (; bits; bits &= bits - 1) {
-                const int k = w * 32 + __builtin_ctz(bits);
-                fn((wm * MT + k / (NT * 4)) * 16 + le_16, tile_channel(false, (k >> 2) % NT, le_grp * 4 + (k & 3)));
+                for (int v = 0; v < 4; ++v) worst = max(worst, __float_as_uint(fabsf(acc[mt][nt][v]) - thr[v]));
             }
         }
-    };
+        if (__any(worst >= 0x7f800000u)) {
+            const int ln = lane_again();
+            // the same without the tile's positions that are no outputs, some of them sums of nothing
+            worst = 0;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                size_t o;
+                if (!out_pos((wm * MT + mt) * 16 + (ln & 15), o)) continue;
+                int here = 0;                 // keeps the loads below in their place
+                asm volatile("" : "+s"(here));
+                const float* const sc = w_scale + here;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    floatx4 e, wl;
+                    load_scale(sc, nt, ln, e, wl);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        worst = max(worst, __float_as_uint(fabsf(acc[mt][nt][v]) - kCert * (l_all + x_all * wl[v]) * e[v]));
+                }
+            }
+        }
+        if (__any(worst >= 0x7f800000u)) {
+            const int ln = lane_again();
+            float l[MT], x[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) l[mt] = x[mt] = 0.f;
+            const char* rec = halo0 + (TW == 8 ? (((ln & 15) >> 3) << row_lg) * HW + (ln & 7) : ln & 15) * PITCH + kLossAt;
+#pragma nounroll
+            for (int a = 0; a < fh; ++a)
+#pragma nounroll
+                for (int b = 0; b < fw; ++b)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const float2 q = *reinterpret_cast<const float2*>(rec + (tile_off(mt) + (a * tap_row + b) * PITCH));
+                        l[mt] += q.x;
+                        x[mt] = fmaxf(x[mt], q.y);
+                    }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                size_t o;
+                const bool ok = out_pos((wm * MT + mt) * 16 + (ln & 15), o);
+                int here = 0;
+                asm volatile("" : "+s"(here));
+                const float* const sc = w_scale + here;
+                // bit nt 4 + v: output v of tile (mt, nt).  (Padded channels have zero weights and no
+                // threshold; an infinity makes them NaN, which a projection would add.)
+                uint32_t bad = 0;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    floatx4 e, wl;
+                    load_scale(sc, nt, ln, e, wl);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        // (explicit fmas: the same decision in every instantiation)
+                        const float d = fmaf(-kCert * fmaf(x[mt], wl[v], l[mt]), e[v], fabsf(acc[mt][nt][v]));
+                        bad |= (uint32_t)(__float_as_uint(d) >= 0x7f800000u) << (nt * 4 + v);
+                    }
+                }
+                if (!ok) bad = 0;
+                if constexpr (EPI == kEpiPool) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        if (!__any(bad >> (nt * 4) & 15)) continue;
+                        floatx4 sum[1];
+                        exact_sums(mt, nt, ln, sum, std::integral_constant<int, 2>{});
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[mt][nt][v] = bad >> (nt * 4 + v) & 1 ? sum[0][v] : acc[mt][nt][v];
+                    }
+                } else {
+                    redo |= __any(bad != 0);
+                    *bad_mask(mt, ln) = (uint16_t)bad;
+                }
+            }
+        }
+    }
     // first channel of the lane's run of four in tile nt
     auto chan = [&](int nt) { return n_base + tile_channel(BF16, nt, le_grp * 4); };
     // The stores of one activation (a compile-time constant, so the per-value
@@ -710,12 +894,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                         if (chan(nt) + v < Cout) store_elem(dst + chan(nt) + v, acc[mt][nt][v]);
             }
         }
-        if constexpr (!BF16)
-            for_each_bad([&](int m, int n) {
-                size_t o;
-                if (out_pos(m, o) && n_base + n < Cout)
-                    store_elem(out + o * Cout + n_base + n, activate(ACT, plain_sum(m, n_base + n) + bias[n_base + n]));
-            });
     };
     // The following 1x1 convolution folded into this epilogue (kEpiProj): per output
     // sample and projection channel o (four, zero padded), the partial dot
@@ -786,18 +964,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const float s1 = __uint_as_float(r1[0]) + __uint_as_float(r1[1]);
             // even and odd groups: the even ones keep the first of their two outputs
             const auto r2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
-            float sum = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
-            if constexpr (!BF16) {
-                // a sample with a marked channel: its whole group again, output le_grp
-                const uint64_t any = __ballot((bad[mt * NT * 4 / 32] >> (mt * NT * 4 % 32)) & ((1ull << (NT * 4)) - 1));
-                if ((any | any >> 16 | any >> 32 | any >> 48) >> le_16 & 1) {
-                    sum = 0.f;
-#pragma nounroll
-                    for (int n = n_base; n < min(n_base + 16 * NT, Cout); ++n)
-                        sum += activate(ACT, plain_sum(wm * 16 * MT + mt * 16 + le_16, n) + bias[n]) *
-                               w2[4 * (size_t)n + le_grp];
-                }
-            }
+            const float sum = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
             if (ok) part_g[o * 4 + le_grp] = sum;
         }
     };
@@ -832,11 +999,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     *reinterpret_cast<floatx4*>(tl + m * POOL_PITCH + (nt - n2) * 16 + le_grp * 4) = a;
                 }
             }
-            if constexpr (!BF16)   // this lane's own values
-                for_each_bad([&](int m, int n) {
-                    if (n >> 5 == n2 >> 1 && n_base + n < Cout)
-                        tl[m * POOL_PITCH + (n & 31)] = activate(ACT, plain_sum(m, n_base + n) + bias[n_base + n]);
-                });
             __syncthreads();
             // a thread takes channels 4 cq .. of every 32nd window; (xq, xr) = window x div and mod k
             const int cq = tid % CQ, c0 = n_base + n2 * 16 + cq * 4;
@@ -864,7 +1026,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         // the bias once, ahead of the activations' code, in place
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const floatx4 b = *reinterpret_cast<const floatx4*>(bias + chan(nt));
+            int here = 0;                     // keeps the load in its place
+            asm volatile("" : "+s"(here));
+            const floatx4 b = *reinterpret_cast<const floatx4*>(bias + here + chan(nt));
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[mt][nt] += b;
         }
@@ -884,14 +1048,68 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         epilogue(std::integral_constant<int, 2>{});
     else
         epilogue(std::integral_constant<int, 0>{});
+    if constexpr (!BF16 && EPI != kEpiPool) {
+        if (!redo) return;
+        // what has failed, over what the epilogue stored: single outputs, or (kEpiProj) the
+        // group's projections of a sample with a failed channel, from all its exact sums
+#pragma nounroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int ln = lane_again();
+            const uint32_t bad = *bad_mask(mt, ln);
+            const uint64_t any = __ballot(bad != 0);
+            if (any == 0) continue;
+            size_t o;
+            const bool ok = out_pos((wm * MT + mt) * 16 + (ln & 15), o);
+            int here = 0;                     // keeps the loads below in their place
+            asm volatile("" : "+s"(here));
+            const float* const bias_p = bias + here;
+            if constexpr (EPI == kEpiStore) {
+#pragma nounroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (!__any(bad >> (nt * 4) & 15)) continue;
+                    floatx4 sum[1];
+                    exact_sums(mt, nt, ln, sum, std::integral_constant<int, 4>{});
+                    const int c = n_base + tile_channel(false, nt, (ln >> 4) * 4);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (c + v < Cout && (bad >> (nt * 4 + v) & 1))
+                            store_elem(out + o * Cout + c + v, activate(act, sum[0][v] + bias_p[c + v]));
+                }
+            } else {
+                const float* const w2_p = w2 + here;
+                floatx4 sum[NT];
+                exact_sums(mt, 0, ln, sum, std::integral_constant<int, 2>{});
+                float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = n_base + tile_channel(false, nt, (ln >> 4) * 4 + v);
+                        const float a = c < Cout ? activate(act, sum[nt][v] + bias_p[c]) : 0.f;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) ps[q] += a * w2_p[4 * (size_t)c + q];
+                    }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    ps[q] += __shfl_xor(ps[q], 16);
+                    ps[q] += __shfl_xor(ps[q], 32);
+                }
+                const float p = ln < 16 ? ps[0] : ln < 32 ? ps[1] : ln < 48 ? ps[2] : ps[3];
+                if (ok && ((any | any >> 16 | any >> 32 | any >> 48) >> (ln & 15) & 1))
+                    part[(size_t)(nb * WGN + wn) * part_stride + o * 4 + (ln >> 4)] = p;
+            }
+        }
+    }
 }
 
 // e_n, the power of two at or below the largest finite magnitude of channel n's
 // weights (at least 2^-112, so that the weights' scale 2^14 / e_n is finite; 0 for
-// a channel without any).  One workgroup per channel.
+// a channel without any), and what the weights' parts leave out.  One workgroup per
+// channel.
 __global__ __launch_bounds__(256) void weight_scale_kernel(WeightView wv, int cout, int cin, int taps,
                                                           float* __restrict__ w_scale) {
     __shared__ uint32_t top;
+    __shared__ float loss[256];
     const int n = blockIdx.x;
     if (threadIdx.x == 0) top = 0u;
     __syncthreads();
@@ -904,18 +1122,34 @@ __global__ __launch_bounds__(256) void weight_scale_kernel(WeightView wv, int co
     }
     atomicMax(&top, m);
     __syncthreads();
-    if (threadIdx.x == 0)
-        w_scale[n] = top == 0u ? 0.f : __uint_as_float(max(top & 0x7f800000u, 15u << 23));
+    const float e = top == 0u ? 0.f : __uint_as_float(max(top & 0x7f800000u, 15u << 23));
+    float sum = 0.f;
+    for (int64_t i = threadIdx.x; e > 0.f && i < count; i += 256) {
+        const int64_t c = i / taps;
+        const float w[8] = {wv.w[(int64_t)n * wv.sn + c * wv.sc + (i - c * taps)], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        sum += split_loss(w, 16384.f / e);
+    }
+    loss[threadIdx.x] = sum;
+    for (int d = 128; d >= 1; d >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < d) loss[threadIdx.x] += loss[threadIdx.x + d];
+    }
+    if (threadIdx.x == 0) {
+        w_scale[2 * n] = e;
+        w_scale[2 * n + 1] = loss[0];
+    }
 }
 
 // Packs a convolution's weights into the order the kernel's lanes load: slices
 // [N block of rows][chunk][th][tw] of rows / 16 tiles, each 64 lanes x 16 bytes per
-// part (lane 16 g + r: channels 8 g .. 8 g + 7 of row r).  One thread per lane of a
-// tile; rows and channels past the layer's are zero.
+// part (lane 16 g + r: channels 8 g .. 8 g + 7 of row r); w32: the values themselves,
+// 32 bytes a lane.  One thread per lane of a tile; rows and channels past the layer's
+// are zero.
 template <bool BF16>
 __global__ __launch_bounds__(256) void pack_weights_kernel(WeightView wv, int cout, int cin, int taps, int rows,
                                                           int nchunks, const float* __restrict__ w_scale,
-                                                          u32x4* __restrict__ dst, int64_t nthreads) {
+                                                          u32x4* __restrict__ dst, floatx4* __restrict__ w32,
+                                                          int64_t nthreads) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= nthreads) return;
     const int lane = (int)(idx & 63), tiles = rows >> 4;
@@ -942,9 +1176,11 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(WeightView wv, int co
         dst[tile_index * 64 + lane] = __builtin_bit_cast(u32x4, h);
     } else {
         u32x4 hi, lo;
-        split_f16(v, n < cout && w_scale[n] > 0.f ? 16384.f / w_scale[n] : 0.f, hi, lo);
+        split_f16(v, n < cout && w_scale[2 * n] > 0.f ? 16384.f / w_scale[2 * n] : 0.f, hi, lo);
         dst[tile_index * 128 + lane] = hi;
         dst[tile_index * 128 + 64 + lane] = lo;
+        w32[(tile_index * 64 + lane) * 2] = floatx4{v[0], v[1], v[2], v[3]};
+        w32[(tile_index * 64 + lane) * 2 + 1] = floatx4{v[4], v[5], v[6], v[7]};
     }
 }
 
@@ -964,10 +1200,11 @@ hipError_t launch_pack_mfma(const PlanConv& pc, hipStream_t s) {
         weight_scale_kernel<<<dim3((unsigned)pc.cout_pad), 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.w_scale);
     if (bf16)
         pack_weights_kernel<true><<<grid, 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.pack_rows,
-                                                       pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w, n);
+                                                       pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w, nullptr, n);
     else
         pack_weights_kernel<false><<<grid, 256, 0, s>>>(pc.wv, pc.cout, pc.cin, pc.fh * pc.fw, pc.pack_rows,
-                                                        pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w, n);
+                                                        pc.cin_pad / kCC, pc.w_scale, (u32x4*)pc.w,
+                                                        (floatx4*)pc.w32, n);
     return hipGetLastError();
 }
 
@@ -1187,19 +1424,21 @@ static hipError_t run_mfma(const void* in, int F, int Hin, int Win, int dil_h, i
     const int Hout = Hin + 2 * pad_h - dil_h * (pc.fh - 1), Wout = Win + 2 * pad_w - dil_w * (pc.fw - 1);
     if (EPI == kEpiProj && (padded || !pc.w2)) return hipErrorInvalidValue;
     const int64_t part_stride = EPI == kEpiProj ? (int64_t)F * Hout * Wout * 4 : 0;
+    // what K binary32 additions lose as a random walk: sqrt(K) 2^-24 of the sum
+    const float cert = 16777216.f / std::sqrt((float)pc.fh * (float)pc.fw * (float)pc.cin);
     if (L.flat) {
         // one "fragment" of 1 x (F * Hin * Win) samples for the staging and the tile grid
         const int flat_len = (int)((int64_t)F * Hin * Win);   // below 2^30 in flat mode
         kern<<<dim3((unsigned)L.nblocks), kThreads, L.t.lds, s>>>(
             (const char*)in, 1, flat_len, pc.cin, (const char*)pc.w, pc.pack_rows, pc.b, pc.fh, pc.fw, pc.cout, pc.act, nchunks,
             (Tout*)out, Hout, Wout, 1, L.t.TW, 1, L.tilesX, nbs, L.t.dbl, Hin, Win, 1, 1, 0, 0, pc.w2, part,
-            part_stride, L.t.TW, 0, 0, pc.wv, pc.w_scale);
+            part_stride, L.t.TW, 0, 0, pc.w32, cert, pc.w_scale);
         return hipGetLastError();
     }
     kern<<<dim3((unsigned)L.nblocks), kThreads, L.t.lds, s>>>(
         (const char*)in, Hin, Win, pc.cin, (const char*)pc.w, pc.pack_rows, pc.b, pc.fh, pc.fw, pc.cout, pc.act, nchunks,
         (Tout*)out, Hout, Wout, L.t.TH, L.t.TW, L.tilesY, L.tilesX, nbs, L.t.dbl, 0, 0, dil_h, dil_w, pad_h, pad_w,
-        pc.w2, part, part_stride, tile_step_w, pool_k, pool_U, pc.wv, pc.w_scale);
+        pc.w2, part, part_stride, tile_step_w, pool_k, pool_U, pc.w32, cert, pc.w_scale);
     return hipGetLastError();
 }
 

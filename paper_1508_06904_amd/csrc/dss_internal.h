@@ -87,7 +87,6 @@ struct WeightView {
     const float* w = nullptr;
     int64_t sn = 0, sc = 0;
     int flip = 0;
-    int nonfinite = 0;          // some weight is an infinity or NaN
 };
 
 struct PlanConv {
@@ -99,11 +98,13 @@ struct PlanConv {
     float* b = nullptr;         // device bias [cout_pad], zero padded
     int pack_rows = 0;          // MFMA kernels: output channels per packed weight slice (the plan's bn; a
                                 // launch with a narrower N tile reads parts of the slices)
-    // binary32 MFMA kernel: the weights as given (its non-finite outputs are summed
-    // again from them) and, device [cout_pad], the power of two e_n that every output
-    // channel's weights were divided by for their binary16 parts
-    WeightView wv;
+    WeightView wv;              // MFMA kernels: what w is packed from (while the plan is made)
+    // binary32 MFMA kernel, device: per output channel the power of two e_n that its
+    // weights were divided by for their binary16 parts and what these parts leave
+    // out, [cout_pad][2]; and the weights in binary32, in the order of w's tiles, from
+    // which outputs whose sums the parts may have spoilt are summed again
     float* w_scale = nullptr;
+    float* w32 = nullptr;
     // MFMA convolution followed by a folded 1x1 projection: its weights as
     // [cout_pad][4] binary32 (zero padded), device
     float* w2 = nullptr;
@@ -173,7 +174,7 @@ struct dss_plan {
     std::vector<dss::PlanConv> convs;     // one per chain layer (impl unused if no conv)
     std::vector<dss::PlanConv> bconvs;    // binary32 plans: the input-gradient convolutions (transposed,
                                           // flipped filters, no bias, no activation)
-    std::vector<float*> wraw;             // binary32 plans: each convolution's weights as given, device
+    std::vector<float*> wraw;             // while the plan is made: each convolution's weights as given, device
     // The last chain layer is a 1x1 convolution to at most 4 channels without a
     // pool, after an MFMA convolution without a pool: dense and mixed
     // evaluations fold it into that convolution's epilogue (convs[L-2].w2) and
@@ -303,7 +304,7 @@ hipError_t allow_dynamic_lds(const void* kern, size_t bytes);
 bool mfma_supports(int fh, int fw);
 int mfma_pick_bn(int cout);
 size_t mfma_packed_bytes(const PlanConv& pc);
-// Packs pc.wv into pc.w (and pc.w_scale, binary32) on the device.
+// Packs pc.wv into pc.w (binary32: also pc.w_scale and pc.w32) on the device.
 hipError_t launch_pack_mfma(const PlanConv& pc, hipStream_t s);
 
 uint16_t host_f32_to_bf16(float f);
