@@ -299,7 +299,7 @@ constexpr int kKC = 32;               // positions per chunk
 constexpr int kWP = kWT + 32;         // LDS row pitch in floats: the two half-waves of a read
                                       // (rows p and p + 1) hit disjoint banks
 constexpr int kMaxTT = 8;             // taps of one filter row per workgroup
-constexpr int kMaxSplitTT = 7;        // the same for the binary16-part kernel (accumulators and shifted operands)
+constexpr int kMaxSplitTT = 7;        // the same for the bfloat16-part kernel (accumulators and shifted operands)
 constexpr int kMaxPackedTT = 4;       // MFMA tiles per wave in the packed (narrow-layer) mode
 
 static size_t wgrad_lds_bytes(int tt) { return 2 * (size_t)(kKC + kKC + tt - 1) * kWP * sizeof(float); }
@@ -473,22 +473,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
     }
 }
 
-// ------------------------------------------------------------------ wgrad on binary16 parts
+// ------------------------------------------------------------------ wgrad on bfloat16 parts
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int kSC = 64;                    // positions per chunk
+constexpr int kSParts = 3;
 constexpr int kSRow = 2 * kWT + 16;        // LDS bytes per staged position and part (the 16 bytes put the four
                                            // rows of a transposing read on different banks)
 constexpr int kSRowsX = kSC + 8;           // staged x positions (taps read up to 7 further on)
 constexpr int kSPlaneA = kSC * kSRow, kSPlaneB = kSRowsX * kSRow;
-constexpr int kSBuf = 2 * (kSPlaneA + kSPlaneB);   // hi and lo parts of dy and x
-constexpr int kSLds = 2 * kSBuf + 64;              // two buffers and the control words
+constexpr int kSLds = kSParts * (kSPlaneA + kSPlaneB) + 64;   // the parts of dy and x, and the flags
 
 // n / d for 0 <= n < 2^31 and a divisor of at least 2 (multiplication by its rounded-up reciprocal)
 struct FastDiv {
@@ -502,21 +502,27 @@ static FastDiv fast_div(uint32_t d) {
 __device__ __forceinline__ uint32_t div_by(uint32_t n, FastDiv f) { return __umulhi(n, f.mul) >> f.shift; }
 
 // The same weight gradient (unpacked layers, channels in fours) with every operand
-// split into two binary16 numbers under a power-of-two scale, three
-// v_mfma_f32_16x16x32_f16 per product (see conv_mfma.hip): the contraction runs
-// over the positions, 32 per issue.  The matrix instruction wants eight
-// consecutive positions of one channel per lane; the chunk is staged as it lies in
-// memory, positions of 64 channels, and read by the transposing LDS loads
-// (ds_read_b64_tr_b16: four positions of a lane's channel).  A lane reads 16
-// positions of x once and shifts them in registers for every tap.
+// split into three bfloat16 numbers, v = b0 + b1 + b2 with b0 = bf16(v), b1 =
+// bf16(v - b0), b2 = bf16(v - b0 - b1): together they hold all 24 bits, and a product
+// is b0 b0 + b0 b1 + b1 b0 + b1 b1 + b0 b2 + b2 b0 (what is left out is below 2^-24 of
+// it), six v_mfma_f32_16x16x32_bf16.  bfloat16 has binary32's exponents, so channels
+// and positions of any magnitude stand side by side without a scale.  (Two binary16
+// parts and three products under one scale per operand take half the matrix cycles,
+// but lose what is 2^-15 and less of the scale's largest value, and real gradients have
+// channels that are hardly ever active beside busy ones.)
 //
-// One scale per operand and workgroup, since a product's positions must share it:
-// the first chunk's largest magnitude goes to [2^12, 2^13), and a later chunk that
-// would exceed binary16 lowers the scale (the accumulators follow, exactly).  The
-// values of a chunk are converted with the scale at hand; a thread that meets one
-// too large says so in LDS, and after the barrier that the chunk needs anyway all
-// threads convert it again, from their registers.  Workgroups that met an infinity
-// or NaN set their flag, and the binary32 kernel computes their sums again.
+// The contraction runs over the positions, 32 per issue.  The matrix instruction wants
+// eight consecutive positions of one channel per lane; the chunk is staged as it lies
+// in memory, positions of 64 channels, and read by the transposing LDS loads
+// (ds_read_b64_tr_b16: four positions of a lane's channel).  A lane reads 16 positions
+// of x once and shifts them in registers for every tap.  The next chunk's loads are in
+// flight while a chunk is computed; its parts go to the same LDS buffer, so that two
+// workgroups fit a CU, one computing while the other converts.
+//
+// Infinities have no finite parts, magnitudes below 2^-117 parts below bfloat16's
+// subnormal numbers (which the instruction takes), and products near binary32's
+// largest parts that may overflow both ways: workgroups that met such values set their
+// flag, and the binary32 kernel computes their sums again.
 template <int TT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_split_kernel(
     const float* __restrict__ dy, const float* __restrict__ x, int E_h, int E_w, int U_w, int Cout, int Cin, int fh,
@@ -524,10 +530,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
     uint32_t* __restrict__ flags, float* __restrict__ partial, float* __restrict__ bias_partial) {
     extern __shared__ __attribute__((aligned(16))) float wl[];
     char* const lds = reinterpret_cast<char*>(wl);
-    // control words: largest dy and x that did not fit, for chunks of even ([0], [1]) and
-    // odd ([2], [3]) number (a wave may be a barrier ahead of another's reading them), and
-    // [4] whether a value was not finite
-    uint32_t* const ctl = reinterpret_cast<uint32_t*>(lds + 2 * kSBuf);
+    uint32_t* const flag = reinterpret_cast<uint32_t*>(lds + kSLds - 64);
     const int total = gridDim.x;
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int q8 = total / 8, r8 = total % 8;
@@ -579,180 +582,148 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
                         : floatx4{0.f, 0.f, 0.f, 0.f};
         }
     };
-    // largest magnitude among a thread's values, as bits
-    auto top_bits = [&](const floatx4* r, int n) {
-        uint32_t m = 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(r[k][e]) & 0x7fffffffu);
-        if (m >= 0x7f800000u) {          // the largest finite one
-            ctl[4] = 1u;
-            m = 0;
-            for (int k = 0; k < n; ++k)
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t b = __float_as_uint(r[k][e]) & 0x7fffffffu;
-                    m = max(m, b < 0x7f800000u ? b : 0u);
-                }
-        }
-        return m;
-    };
-    // power of two that takes a largest magnitude with these bits into [2^12, 2^13), at most 2^100
-    auto scale_of = [](uint32_t bits) {
-        return __uint_as_float(min((266u << 23) - (bits & 0x7f800000u), 227u << 23));
-    };
     // The matrix instruction rounds its sums down a little (the mean error of a sum
     // is negative, whatever its sign), which over the positions of all splits would
-    // add up: 1.1e-6 of the gradient over 2^20 positions, beside 5e-7 of scatter.
-    // Every other split therefore sums -dy x, and its sums are negated back.
-    const float sign = split & 1 ? -1.f : 1.f;
-    float sa = 1.f, sb = 1.f;
-    auto store_part = [&](char* plane, int plane_bytes, int row, floatx4 r, float scale) {
-        f16x4 h, l;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float v = r[e] * scale;
-            h[e] = (_Float16)v;
-            l[e] = (_Float16)(v - (float)h[e]);
-        }
+    // add up.  Every other split therefore sums -dy x, and its sums are negated back.
+    const uint32_t sign = split & 1 ? 0x80000000u : 0u;
+    uint32_t low = ~0u;                    // twice the smallest magnitude but 0, less 1
+    float high_a = 0.f, high_b = 0.f;      // the largest magnitudes (NaN, which stays NaN in every part, passes by)
+    auto store_parts = [&](char* plane, int plane_bytes, int row, floatx4 r) {
         char* dst = plane + row * kSRow + s_col * 2;
-        *reinterpret_cast<u32x2*>(dst) = __builtin_bit_cast(u32x2, h);
-        *reinterpret_cast<u32x2*>(dst + plane_bytes) = __builtin_bit_cast(u32x2, l);
+#pragma unroll
+        for (int p = 0; p < kSParts; ++p) {
+            bf16x4 b;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                b[e] = (__bf16)r[e];
+                r[e] -= (float)b[e];
+            }
+            *reinterpret_cast<u32x2*>(dst + p * plane_bytes) = __builtin_bit_cast(u32x2, b);
+        }
     };
-    auto store_chunk = [&](int buf) {
-        char* A = lds + buf * kSBuf;
-        char* B = A + 2 * kSPlaneA;
+    auto note = [&](floatx4 r, float& high) {
 #pragma unroll
-        for (int k = 0; k < NA; ++k) store_part(A, kSPlaneA, s_row + 16 * k, ra[k], sa);
+        for (int e = 0; e < 4; ++e) low = min(low, (__float_as_uint(r[e]) << 1) - 1u);
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(high) : "v"(r[0]), "v"(r[1]));
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(high) : "v"(r[2]), "v"(r[3]));
+    };
+    auto store_chunk = [&] {
+        char* const A = lds;
+        char* const B = lds + kSParts * kSPlaneA;
 #pragma unroll
-        for (int k = 0; k < NB; ++k)
-            if (s_row + 16 * k < kSRowsX) store_part(B, kSPlaneB, s_row + 16 * k, rb[k], sb);
+        for (int k = 0; k < NA; ++k) {
+            note(ra[k], high_a);
+            floatx4 r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(__float_as_uint(ra[k][e]) ^ sign);
+            store_parts(A, kSPlaneA, s_row + 16 * k, r);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            note(rb[k], high_b);
+            if (s_row + 16 * k < kSRowsX) store_parts(B, kSPlaneB, s_row + 16 * k, rb[k]);
+        }
     };
 
     // db[o] = sum_p dy[p][o]: the workgroups of the first input tile, tap row and tap group add their dy rows
     const bool do_bias = it == 0 && tg == 0 && th == 0;
     floatx4 bsum = {0.f, 0.f, 0.f, 0.f};
-    auto add_bias = [&] {
-        if (do_bias) {
-#pragma unroll
-            for (int k = 0; k < NA; ++k) bsum += ra[k];
-        }
-    };
-
-    if (tid < 5) ctl[tid] = 0u;
-    __syncthreads();
-    if (c0 < c1) {
-        load_chunk(c0);
-        uint32_t ma = top_bits(ra, NA), mb = top_bits(rb, NB);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            ma = max(ma, (uint32_t)__shfl_xor((int)ma, d));
-            mb = max(mb, (uint32_t)__shfl_xor((int)mb, d));
-        }
-        if (lane == 0) {
-            atomicMax(&ctl[0], ma);
-            atomicMax(&ctl[1], mb);
-        }
-        __syncthreads();
-        sa = sign * scale_of(ctl[0]);
-        sb = scale_of(ctl[1]);
-        __syncthreads();
-        if (tid < 2) ctl[tid] = 0u;
-        store_chunk(0);
-        add_bias();
-    }
-    __syncthreads();
+    if (tid < 3) flag[tid] = 0u;
+    if (c0 < c1) load_chunk(c0);
     // transposing reads: lane j of group g reads positions 8 g + j / 4, channels 4 (j % 4) .. + 3
     // of a 16-channel tile, and receives four positions of channel j
     const int tr_off = (8 * grp + (l16 >> 2)) * kSRow + (l16 & 3) * 8;
     auto tr_read = [&](const char* p) {
         return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
     };
+    const char* const A = lds + tr_off + wm * 64;
+    const char* const B = lds + kSParts * kSPlaneA + tr_off + wn * 64;
     for (int c = c0; c < c1; ++c) {
-        const int buf = (c - c0) & 1;
-        const bool more = c + 1 < c1;
-        if (more) load_chunk(c + 1);
-        const char* A = lds + buf * kSBuf + tr_off + wm * 64;
-        const char* B = lds + buf * kSBuf + 2 * kSPlaneA + tr_off + wn * 64;
+        __syncthreads();                       // every wave is done with the chunk before
+        store_chunk();
+        if (do_bias) {
+#pragma unroll
+            for (int k = 0; k < NA; ++k) bsum += ra[k];
+        }
+        __syncthreads();
+        if (c + 1 < c1) load_chunk(c + 1);
 #pragma unroll
         for (int ks = 0; ks < kSC / 32; ++ks) {
-            f16x8 a[2][2];
+            bf16x8 a[2][kSParts];
 #pragma unroll
             for (int oi = 0; oi < 2; ++oi)
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
+                for (int p = 0; p < kSParts; ++p) {
                     const char* src = A + p * kSPlaneA + ks * 32 * kSRow + oi * 32;
                     const u32x2 lo = tr_read(src), hi = tr_read(src + 4 * kSRow);
-                    a[oi][p] = __builtin_bit_cast(f16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+                    a[oi][p] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
                 }
 #pragma unroll
             for (int ii = 0; ii < 2; ++ii) {
-                // 16 positions of the lane's channel per part, and the same one position on
-                uint32_t even[2][8], odd[2][8];
+                __builtin_amdgcn_sched_barrier(0);
+                // the smallest parts of x first; with part pb, dy's parts 2 - pb .. 0
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const char* src = B + p * kSPlaneB + ks * 32 * kSRow + ii * 32;
+                for (int pb = kSParts - 1; pb >= 0; --pb) {
+                    // 16 positions of the lane's channel, and the same one position on
+                    uint32_t even[8], odd[8];
+                    const char* src = B + pb * kSPlaneB + ks * 32 * kSRow + ii * 32;
 #pragma unroll
                     for (int k = 0; k < (TT > 1 ? 4 : 2); ++k) {
                         const u32x2 v = tr_read(src + 4 * k * kSRow);
-                        even[p][2 * k] = v[0];
-                        even[p][2 * k + 1] = v[1];
+                        even[2 * k] = v[0];
+                        even[2 * k + 1] = v[1];
                     }
                     if constexpr (TT > 1) {
 #pragma unroll
-                        for (int k = 0; k < 7; ++k)
-                            odd[p][k] = __builtin_amdgcn_alignbit(even[p][k + 1], even[p][k], 16);
+                        for (int k = 0; k < 7; ++k) odd[k] = __builtin_amdgcn_alignbit(even[k + 1], even[k], 16);
                     }
-                }
-                auto tap = [&](int t, int p) {
-                    const uint32_t* r = t & 1 ? odd[p] : even[p];
-                    const int k = t >> 1;
-                    return __builtin_bit_cast(f16x8, u32x4{r[k], r[k + 1], r[k + 2], r[k + 3]});
-                };
-                // the smallest products first
+                    auto tap = [&](int t) {
+                        const uint32_t* q = t & 1 ? odd : even;
+                        const int k = t >> 1;
+                        return __builtin_bit_cast(bf16x8, u32x4{q[k], q[k + 1], q[k + 2], q[k + 3]});
+                    };
+                    // b2's product goes to the sums; b1's two and b0's three are added up from zero first, so that
+                    // 32 positions round a sum three times instead of six (relative error of N(0,1) gradients
+                    // over 93,000 positions 7.0e-7 -> 3.7e-7, on the binary32 instruction 8.2e-7; 5 % of a
+                    // gradient step's time)
 #pragma unroll
-                for (int t0 = 0; t0 < TT; t0 += 2)
+                    for (int t0 = 0; t0 < TT; t0 += 2) {
+                        floatx4 sum[2][2];
 #pragma unroll
-                    for (int pr = 0; pr < 3; ++pr)
+                        for (int pa = kSParts - 1 - pb; pa >= 0; --pa)
+#pragma unroll
+                            for (int t = t0; t < (t0 + 2 < TT ? t0 + 2 : TT); ++t)
+#pragma unroll
+                                for (int oi = 0; oi < 2; ++oi) {
+                                    const floatx4 from = pb == kSParts - 1         ? acc[t][oi][ii]
+                                                         : pa == kSParts - 1 - pb ? floatx4{0.f, 0.f, 0.f, 0.f}
+                                                                                  : sum[t - t0][oi];
+                                    sum[t - t0][oi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[oi][pa], tap(t), from, 0, 0, 0);
+                                }
 #pragma unroll
                         for (int t = t0; t < (t0 + 2 < TT ? t0 + 2 : TT); ++t)
 #pragma unroll
-                            for (int oi = 0; oi < 2; ++oi)
-                                acc[t][oi][ii] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                    a[oi][pr == 0], tap(t, pr == 1), acc[t][oi][ii], 0, 0, 0);
+                            for (int oi = 0; oi < 2; ++oi) {
+                                if (pb == kSParts - 1) acc[t][oi][ii] = sum[t - t0][oi];
+                                else acc[t][oi][ii] += sum[t - t0][oi];
+                            }
+                    }
+                }
             }
-        }
-        if (more) {
-            const uint32_t ma = top_bits(ra, NA), mb = top_bits(rb, NB);
-            if (__uint_as_float(ma) * fabsf(sa) >= 65504.f) atomicMax(&ctl[2 * buf], ma);
-            if (__uint_as_float(mb) * sb >= 65504.f) atomicMax(&ctl[2 * buf + 1], mb);
-            store_chunk(buf ^ 1);
-            add_bias();
-        }
-        __syncthreads();
-        const uint32_t na = ctl[2 * buf], nb = ctl[2 * buf + 1];
-        if (na | nb) {                        // the chunk does not fit its scale: lower it, convert again
-            const float fa = na ? sign * scale_of(na) : sa, fb = nb ? scale_of(nb) : sb;
-            const float down = (fa / sa) * (fb / sb);
-            sa = fa;
-            sb = fb;
-#pragma unroll
-            for (int t = 0; t < TT; ++t)
-#pragma unroll
-                for (int oi = 0; oi < 2; ++oi)
-#pragma unroll
-                    for (int ii = 0; ii < 2; ++ii) acc[t][oi][ii] *= down;
-            __syncthreads();                  // everyone has read the control words
-            if (tid < 2) ctl[2 * buf + tid] = 0u;
-            store_chunk(buf ^ 1);
-            __syncthreads();
         }
     }
 
-    if (tid == 0) flags[id] = ctl[4];
+    if (low < ((10u << 23) << 1) - 1u) *flag = 1u;       // 2^-117
+    atomicMax(flag + 1, __float_as_uint(high_a));
+    atomicMax(flag + 2, __float_as_uint(high_b));
+    __syncthreads();
+    if (tid == 0) {
+        // (what bfloat16 rounds to infinity, or products of parts that may be infinities of both signs)
+        const float a = __uint_as_float(flag[1]), b = __uint_as_float(flag[2]);
+        flags[id] = *flag != 0u || !(fmaxf(a, b) < __uint_as_float(0x7f7f8000u)) || a * b >= 0x1p120f ? 1u : 0u;
+    }
     if (do_bias) {
         // rows s_row of the 16 column quads, added in order
-        __syncthreads();
         *reinterpret_cast<floatx4*>(lds + tid * 16) = bsum;
         __syncthreads();
         if (tid < kWT && o0 + tid < Cout) {
@@ -762,7 +733,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
             bias_partial[(size_t)split * Cout + o0 + tid] = s;
         }
     }
-    const float ua = 1.f / sa, ub = 1.f / sb;
     const int taps = fh * fw;
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
@@ -776,7 +746,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void w
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int o = o0 + wm * 32 + oi * 16 + grp * 4 + v;
-                    if (o < Cout && i < Cin) dst[(size_t)o * Cin + i] = acc[t][oi][ii][v] * ua * ub;
+                    if (o < Cout && i < Cin)
+                        dst[(size_t)o * Cin + i] = __uint_as_float(__float_as_uint(acc[t][oi][ii][v]) ^ sign);
                 }
             }
     }
@@ -809,10 +780,10 @@ __global__ __launch_bounds__(kBT) void wgrad_reduce_kernel(const float* __restri
 
 WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw) {
     WgradPlan w;
-    // the binary16-part kernel: whole float4 channel groups, and rows that its division takes
+    // the bfloat16-part kernel: whole float4 channel groups, and rows that its division takes
     // (more than 16 input channels: at 32 its tile is half padding and still faster than two taps side by
-    // side on the binary32 instruction, 0.25 against 0.44 ms for the 5x5 32 -> 64 layer of a 512 x 512
-    // signal; at 16 four taps fill that one's tile)
+    // side on the binary32 instruction, 0.167 against 0.238 ms for a 5x5 32 -> 64 layer of 255 x 255 samples,
+    // 0.087 against 0.111 for a 1x1 one; at 16 four taps fill that one's tile and the two are 5 % apart)
     w.split = Cin > kWT / 4 && Cout % 4 == 0 && Cin % 4 == 0 && E_w + fw - 1 >= 2;
     if (Cin <= kWT / 2 && !w.split) {
         // packed: cpt columns per tap, g taps per tile; at most kMaxPackedTT tiles,

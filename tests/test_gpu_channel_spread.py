@@ -171,3 +171,42 @@ def test_signal_gradient_of_different_output_channels():
     flipped = [{"kind": "conv", "cin": 72, "cout": 32, "fh": 5, "fw": 5, "act": "none", "bias": np.zeros(32, np.float32),
                 "weight": np.ascontiguousarray(w.layers[0]["weight"].transpose(1, 0, 2, 3)[:, :, ::-1, ::-1])}]
     check(gx.cpu().numpy().astype(np.float64), *evaluate(flipped, np.pad(G, ((0, 0), (4, 4), (4, 4)))), "signal gradient")
+
+
+# what the weight gradient's operands are made of: channels of x, of dy or of both 2^-30 .. 2^30 apart; single samples
+# of 2^40; dead channels beside live ones; magnitudes whose scales overflow one after the other; a signal that starts
+# 2^-75 of what it becomes in some of its channels
+@pytest.mark.parametrize("data", ["x", "dy", "both", "hot", "dead", "far", "start"])
+@pytest.mark.parametrize("fw", [1, 3, 4, 7])
+def test_weight_gradient_of_different_channels(fw, data):
+    import torch
+    from tests.test_gpu_split import _weight_gradient
+    cin, cout, fh, H, W = (68, 72, 2, 50, 61) if fw % 2 else (36, 64, 1, 70, 83)
+    w = wl.custom([("conv", cin, cout, fh, fw, "none")], cin, H, W, seed=90 + fw, value_kind="normal")
+    rng = np.random.default_rng(91)
+    x, G = w.x, rng.standard_normal((cout, H - fh + 1, W - fw + 1)).astype(np.float32)
+    if data in ("x", "both"):
+        x *= (2.0 ** rng.integers(-30, 31, size=cin))[:, None, None].astype(np.float32)
+    if data in ("dy", "both"):
+        G *= (2.0 ** rng.integers(-30, 31, size=cout))[:, None, None].astype(np.float32)
+    if data == "hot":
+        x[3, H // 2, W // 3] *= np.float32(2.0 ** 40)
+        G[5, H // 3, W // 2] *= np.float32(2.0 ** 40)
+    if data == "dead":
+        x[rng.integers(0, cin, 8)] = 0
+        G[rng.integers(0, cout, 8)] = 0
+        G *= rng.integers(0, 2, size=G.shape)
+    if data == "far":
+        x *= np.float32(2.0 ** -100)
+        G *= np.float32(2.0 ** 120)
+    if data == "start":
+        x[:, :H // 2] *= np.float32(2.0 ** -75)
+        x[::2, H // 2:] = 0
+    plan = dss.Plan(w.layers, 2, cin)
+    gw, gb, _ = plan.backward(to_device(x, "f32"), to_device(G, "f32"), with_signal_grad=False)
+    torch.cuda.synchronize()
+    got = plan.split_grads(gw, gb)[0][0].cpu().numpy().astype(np.float64)
+    mag = _weight_gradient(np.abs(x), np.abs(G), fh, fw)
+    check(got, _weight_gradient(x, G, fh, fw), mag, G[0].size, "dW fw %d %s" % (fw, data))
+    if data == "dead":
+        assert (got[mag == 0] == 0).all()
