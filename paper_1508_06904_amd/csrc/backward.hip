@@ -784,7 +784,9 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
     // (more than 16 input channels: at 32 its tile is half padding and still faster than two taps side by
     // side on the binary32 instruction, 0.167 against 0.238 ms for a 5x5 32 -> 64 layer of 255 x 255 samples,
     // 0.087 against 0.111 for a 1x1 one; at 16 four taps fill that one's tile and the two are 5 % apart)
-    w.split = Cin > kWT / 4 && Cout % 4 == 0 && Cin % 4 == 0 && E_w + fw - 1 >= 2;
+    const bool vec = Cout % 4 == 0 && Cin % 4 == 0;
+    w.positions = (int64_t)F * E_h * (E_w + fw - 1);
+    w.split = Cin > kWT / 4 && vec && E_w + fw - 1 >= 2 && w.positions + kMaxSplitTT + kSC < (1ll << 31);
     if (Cin <= kWT / 2 && !w.split) {
         // packed: cpt columns per tap, g taps per tile; at most kMaxPackedTT tiles,
         // the fewest MFMA tiles per row (ntg * tt), then the most taps per group
@@ -804,7 +806,7 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
     } else {
         // the largest group of taps (at most kMaxTT) whose ragged last group wastes
         // at most a tenth of the row's MFMA work
-        for (int tt = std::min(fw, w.split ? kMaxSplitTT : kMaxTT); tt >= 1; --tt) {
+        for (int tt = std::min(fw, vec ? kMaxSplitTT : kMaxTT); tt >= 1; --tt) {
             const int ntg = (fw + tt - 1) / tt;
             if (10 * (ntg * tt - fw) <= fw) {
                 w.tt = tt;
@@ -813,7 +815,6 @@ WgradPlan wgrad_plan(int F, int E_h, int E_w, int Cout, int Cin, int fh, int fw)
             }
         }
     }
-    w.positions = (int64_t)F * E_h * (E_w + fw - 1);
     const int64_t chunk = w.split ? kSC : kKC;
     w.nchunks = (w.positions + chunk - 1) / chunk;
     w.otiles = (Cout + kWT - 1) / kWT;
@@ -894,7 +895,9 @@ static hipError_t dispatch_wgrad(const float* dy, const float* x, int E_h, int E
         case 5: return run_wgrad<VEC, 5, false>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, w, partial, bpart, s);
         case 6: return run_wgrad<VEC, 6, false>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, w, partial, bpart, s);
         case 7: return run_wgrad<VEC, 7, false>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, w, partial, bpart, s);
-        case 8: return run_wgrad<VEC, 8, false>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, w, partial, bpart, s);
+        case 8:
+            if constexpr (!VEC)
+                return run_wgrad<VEC, 8, false>(dy, x, E_h, E_w, U_h, U_w, Cout, Cin, fh, fw, w, partial, bpart, s);
     }
     return hipErrorInvalidValue;
 }
@@ -904,7 +907,7 @@ hipError_t launch_wgrad(const float* dy, const float* x, int F, int E_h, int E_w
     (void)F;
     // positions and chunks are 32-bit in the kernel
     const int span = w.packed ? w.tt * (kWT / w.cpt) : w.tt;   // taps per group
-    if (w.positions + span + kSC >= (1ll << 31) || U_w != E_w + fw - 1 || U_h != E_h + fh - 1)
+    if (w.positions + span + (w.split ? kSC : kKC) >= (1ll << 31) || U_w != E_w + fw - 1 || U_h != E_h + fh - 1)
         return hipErrorInvalidConfiguration;
     float* bpart = partial + w.partial_floats;
     const bool vec = Cout % 4 == 0 && Cin % 4 == 0;
