@@ -1223,7 +1223,7 @@ extern "C" dss_status dss_backward_dense(dss_plan_t plan, const void* signal, in
         if (j > 1 && c.c_h == 1 && c.c_w == 1 && c.cout <= 4 && c.cin % 4 == 0 && ch.layers[j - 2].has_conv &&
             !ch.layers[j - 2].has_pool && plan->convs[j - 1].impl == CONV_DIRECT &&
             plan->bconvs[j - 1].impl == CONV_DIRECT) {
-            e = T.run("wgrad_mfma", j, 2.0 * fl, 0.0, [&] {   // the name of every weight gradient's record
+            e = T.run("narrow_backward", j, 2.0 * fl, 0.0, [&] {   // its weight and input gradient
                 return launch_narrow_backward(gb[cur], A(j - 1), plan->convs[j - 1], (int64_t)Fin * lg.E_h * lg.E_w,
                                               ch.layers[j - 2].act, wp, wpart, gb[cur ^ 1], grad_weight + B.wofs[j],
                                               grad_bias + B.bofs[j], stream);
