@@ -17,7 +17,7 @@ import pytest
 
 from paper_1508_06904_amd import build
 
-SOURCES = ["conv_mfma.hip", "backward.hip", "conv_direct.hip", "kernels_data.hip"]
+SOURCES = ["conv_mfma.hip", "backward.hip", "chain_fused.hip", "conv_direct.hip", "kernels_data.hip"]
 
 
 def _report(src):
@@ -58,7 +58,7 @@ def test_no_scratch_and_no_spills(reports, src):
 
 def test_mfma_kernels_keep_two_waves_per_simd(reports):
     mfma = {n: r for src in ("conv_mfma.hip", "backward.hip") for n, r in reports[src].items()
-            if "conv_mfma_kernel" in n or "wgrad_mfma_kernel" in n}
-    assert len(mfma) >= 20
+            if "conv_mfma_kernel" in n or "wgrad_mfma_kernel" in n or "wgrad_split_kernel" in n}
+    assert len(mfma) >= 20 and sum("wgrad_split_kernel" in n for n in mfma) == 7
     for name, r in mfma.items():
         assert r["Occupancy"] >= 2, (name, r)
