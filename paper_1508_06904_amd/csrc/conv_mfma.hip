@@ -1064,16 +1064,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             asm volatile("" : "+s"(here));
             const float* const bias_p = bias + here;
             if constexpr (EPI == kEpiStore) {
-#pragma nounroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    if (!__any(bad >> (nt * 4) & 15)) continue;
-                    floatx4 sum[1];
-                    exact_sums(mt, nt, ln, sum, std::integral_constant<int, 4>{});
+                auto store_failed = [&](int nt, const floatx4& sum) {
                     const int c = n_base + tile_channel(false, nt, (ln >> 4) * 4);
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         if (c + v < Cout && (bad >> (nt * 4 + v) & 1))
-                            store_elem(out + o * Cout + c + v, activate(act, sum[0][v] + bias_p[c + v]));
+                            store_elem(out + o * Cout + c + v, activate(act, sum[v] + bias_p[c + v]));
+                };
+                uint32_t tiles = 0;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) tiles |= (uint32_t)(__any(bad >> (nt * 4) & 15) != 0) << nt;
+                if (tiles == (1u << NT) - 1) {               // channels that differ: all tiles side by side
+                    floatx4 sum[NT];
+                    exact_sums(mt, 0, ln, sum, std::integral_constant<int, 2>{});
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) store_failed(nt, sum[nt]);
+                    continue;
+                }
+#pragma nounroll
+                for (int nt = 0; nt < NT; ++nt) {            // a single output as a rule
+                    if (!(tiles >> nt & 1)) continue;
+                    floatx4 sum[1];
+                    exact_sums(mt, nt, ln, sum, std::integral_constant<int, 4>{});
+                    store_failed(nt, sum[0]);
                 }
             } else {
                 const float* const w2_p = w2 + here;
