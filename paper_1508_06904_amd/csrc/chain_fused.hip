@@ -17,8 +17,8 @@
 //
 // Bound by LDS latency and the vector ALU of the busiest CU: several positions of a
 // thread share each weight read, and the filter loop keeps several reads in
-// flight.  64 x 64 image 50.8 -> 19.6 us an evaluation (fused_plan has the sizes
-// around it).
+// flight.  64 x 64 image 50.8 -> 19.6 us an evaluation (fused_plan has other sizes
+// and networks).
 #include <algorithm>
 #include <type_traits>
 
@@ -277,6 +277,41 @@ static int64_t fused_regions(const Chain& ch, int TH, int TW, FusedChain* fc) {
     return std::max<int64_t>(macs, 1);
 }
 
+// One workgroup's tile: its threads' chains of LDS reads and multiply-adds, layer by layer.
+static double thread_cost(const FusedChain& fc) {
+    double cost = 0.0;
+    for (int j = 0; j < fc.n; ++j) {
+        const FusedLayer& f = fc.L[j];
+        if (!f.has_conv) continue;
+        const bool vec = f.cin % 4 == 0;
+        const int npos = f.e_h * f.e_w, ci = vec ? 4 : 1;
+        const int pp = npos <= kFT ? 1 : vec || npos <= 2 * kFT || f.cob >= 16 ? 2 : 4;      // as in fused_conv
+        const double iters = (double)((npos + kFT * pp - 1) / (kFT * pp)) * (f.cout_pad / f.cob);
+        cost += 2.2 + iters * (0.085 + (double)(f.fh * f.fw * f.cin / ci) * (0.04 + 0.0078 * ci * pp * f.cob));
+    }
+    return cost;
+}
+
+// The separate launches: their number, the longest chain of each convolution's threads,
+// and its operations and input reads.
+static double separate_cost(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, int out_w, double conv_flops,
+                            int launches) {
+    double cost = 5.8 * launches + 3e-8 * conv_flops;
+    int64_t h = out_h, w = out_w;
+    for (int j = ch.L(); j >= 1; --j) {
+        const ChainLayer& c = ch.layers[j - 1];
+        h += (int64_t)ch.kstar_h[j - 1] * (c.k_h - 1);
+        w += (int64_t)ch.kstar_w[j - 1] * (c.k_w - 1);
+        if (c.has_conv) {
+            const double K = (double)c.cin * c.c_h * c.c_w;
+            cost += 0.13 * K + 3.2e-7 * h * w * K * (convs[j - 1].cout_pad / convs[j - 1].cob);
+        }
+        h += (int64_t)ch.kstar_h[j - 1] * (c.c_h - 1);
+        w += (int64_t)ch.kstar_w[j - 1] * (c.c_w - 1);
+    }
+    return cost;
+}
+
 bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, int out_w, double conv_flops,
                 FusedChain* fc) {
     const int L = ch.L();
@@ -299,13 +334,20 @@ bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, 
         f.cob = pc.cob;
         f.cout_pad = pc.cout_pad;
     }
-    // The tile that finishes first: two workgroups a CU, each taking about a clock
-    // for 20 multiply-adds and 28,000 for its latencies (barriers, LDS chains, loads).
-    // Measured, conv5x5 1-4, conv5x5 4-8, conv4x4 8-1 network, tiles of 4 / 8 / 16:
-    // 64 x 64 signal 19.6 / 21.0 / 26.2 us, 128 x 128 37.4 / 21.1 / 26.2, 256 x 256
-    // 135 / 47 / 27, 400 x 400 329 / 101 / 52.  Separate launches: 50.8, 51.8, 54.3
-    // and 68.9 us, and 81.6 us for 600 x 500 samples, which the 16-wide tile takes
-    // 77.6 us for: about 17,500 clocks a launch and one for 7,300 operations.
+    // The tile that finishes first, and whether the separate launches finish before it.
+    // Both sides' costs are fitted together to the choices that eleven networks (1 to 4
+    // layers, filters of 2x2 to 11x11, 1 to 16 channels, pools of 2 to 4) on 48 x 48 to
+    // 600 x 800 samples call for, every tile side and the separate launches measured: they
+    // are in one unit, not in microseconds.  Up to 512 tiles run at once, two a CU, and
+    // further ones in whole rounds.  Of those 77 calls 73 take the fastest way or one within
+    // 10 %; the others lose 7 to 17 % to another tile side, none more than 5 % to the separate
+    // launches.  For instance, separate / tiles of 4 / 8 / 16 in us:
+    //   conv5x5 1-4, pool, conv5x5 4-8, pool, conv4x4 8-1   48 x 48    50.5 / 20.5 / 21.1 / 25.9
+    //                                                       400 x 400  68.9 / 329 / 101 / 52.0
+    //                                                       600 x 800  94.7 / 1013 / 295 / 105
+    //   conv3x3 1-12, 12-12, 12-12, pool, conv3x3 12-2      150 x 150  47.7 / 93.4 / 34.9
+    //                                                       200 x 320  58.2 / 242 / 68.2
+    //   conv11x11 3-14, conv5x5 14-1                        200 x 320  91.9 / 496 / 138 / 70.0
     double best = 0.0;
     FusedChain pick = *fc;
     for (int side = 4; side <= 64; side *= 2) {
@@ -314,16 +356,17 @@ bool fused_plan(const Chain& ch, const std::vector<PlanConv>& convs, int out_h, 
         const int64_t macs = fused_regions(ch, TH, TW, &t);
         if (macs == 0) break;
         const int64_t tiles = ceil_div64(out_h, TH) * ceil_div64(out_w, TW);
-        const double clocks = (double)ceil_div64(tiles, 512) * (macs / 20.0 + 28000.0);
-        if (tiles < (1ll << 31) && (best == 0.0 || clocks < best)) {
-            best = clocks;
+        const double cost = (double)ceil_div64(tiles, 512) *
+                            (8.0 + std::max(thread_cost(t), (tiles > 256 ? 2.0 : 1.0) * macs / 48000.0));
+        if (tiles < (1ll << 31) && (best == 0.0 || cost < best)) {
+            best = cost;
             pick = t;
         }
     }
     if (best == 0.0) return false;
     *fc = pick;
     fc->tiles_x = (int)ceil_div64(out_w, fc->TW);
-    return best < 17500.0 * launches + conv_flops / 7300.0;
+    return best < separate_cost(ch, convs, out_h, out_w, conv_flops, launches);
 }
 
 hipError_t launch_fused_chain(const FusedChain& fc, const float* signal, int H, int W, float* out, int out_h, int out_w,

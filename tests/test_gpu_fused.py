@@ -67,3 +67,31 @@ def test_fused_chain_tile_choice(size):
     got, dil = plan.eval_dense(x), plan.eval_dilate(x)
     torch.cuda.synchronize()
     assert torch.equal(got, dil)
+
+
+# calls on either side of the rule (both ways measured: one launch / separate launches in us)
+@pytest.mark.parametrize("arch,C,H,W,fused", [
+    ([("conv", 12, 3, 3, "relu")] + [("conv", 12, 3, 3, "relu")] * 2 + [("pool", 2, 2), ("conv", 2, 3, 3, "none")], 1, 150, 150,
+     True),      # 35 / 48
+    ([("conv", 12, 3, 3, "relu")] + [("conv", 12, 3, 3, "relu")] * 2 + [("pool", 2, 2), ("conv", 2, 3, 3, "none")], 1, 200, 320,
+     False),     # 68 / 58
+    ([("conv", 14, 11, 11, "relu"), ("conv", 1, 5, 5, "none")], 3, 200, 320, True),      # 70 (tiles of 16; 138 of 8) / 92
+    ([("conv", 8, 5, 5, "relu")] * 3, 4, 600, 800, False),                               # 172 / 113
+])
+def test_fused_chain_is_taken_where_it_is_faster(arch, C, H, W, fused):
+    import torch
+    layers, cin = [], C
+    for s in arch:
+        layers.append(("conv", cin) + s[1:] if s[0] == "conv" else s)
+        cin = s[1] if s[0] == "conv" else cin
+    w = wl.custom(layers, C, H, W, seed=82, value_kind="normal")
+    plan = dss.Plan(w.layers, 2, C)
+    x = to_device(w.x, "f32")
+    plan.set_timing(True)
+    got = plan.eval_dense(x)
+    names = [r["kernel"] for r in plan.timings()]
+    plan.set_timing(False)
+    dil = plan.eval_dilate(x)
+    torch.cuda.synchronize()
+    assert (names == ["dense_fused"]) == fused
+    assert torch.equal(got, dil)
