@@ -1245,9 +1245,8 @@ static bool fit_halo(int64_t halo_px, bool bf16, size_t cap, Tile* t) {
 // masked samples on this layer's fragment extent; among those, one whose halo can
 // be double-buffered within the LDS budget of two workgroups per CU, then the
 // smallest halo.  Filters whose halo fits no such budget get the LDS of a whole
-// CU.  The bfloat16 kernel counts the work of an 8-wide tile whose halo row is
-// not 8 mod 16 samples long 3 % higher: the layers where that decides have under
-// 0.3 % of masked work between the two shapes, and 16 x 16 stages a smaller halo.
+// CU.  (8-wide tiles cost no more per sample than wider ones: neither read pattern
+// has bank conflicts.)
 static Tile pick_tile(int Hout, int Wout, int fh, int fw, size_t lds_max, bool bf16) {
     Tile best{0, 0, 0, 0};
     for (const size_t cap : {std::min(lds_max, (size_t)kMaxLds), std::min(lds_max, (size_t)kMaxLds1)}) {
@@ -1257,8 +1256,7 @@ static Tile pick_tile(int Hout, int Wout, int fh, int fw, size_t lds_max, bool b
             const int64_t halo_px = (int64_t)(TH + fh - 1) * (TW + fw - 1);
             Tile t{TH, TW, 0, 0};
             if (!fit_halo(halo_px, bf16, cap, &t)) continue;
-            int64_t work = ceil_div64(Hout, TH) * TH * ceil_div64(Wout, TW) * TW;
-            if (bf16 && TW < 16 && (TW + fw - 1) % 16 != 8) work += work / 32;
+            const int64_t work = ceil_div64(Hout, TH) * TH * ceil_div64(Wout, TW) * TW;
             const bool better = best_work < 0 || work < best_work ||
                                 (work == best_work && (t.dbl > best.dbl || (t.dbl == best.dbl && halo_px < best_halo)));
             if (better) {
@@ -1343,13 +1341,17 @@ static LaunchShape launch_shape(bool bf16, int F, int Hin, int Win, int dil_h, i
 
 // The 128-channel N tile or the 64-channel one for a launch.  A launch of fewer
 // workgroups than the 512 that the GPU holds at once (two per CU) leaves CUs
-// idle or half-loaded; the 64-channel tile doubles the workgroup count at a
-// cost of about 10 % per MFMA in operand traffic (measured on the conv6x6
-// 256->512 layer of a 135 x 240 fragment).  With every workgroup resident, the
-// busiest CU sets the time: ceil(blocks / 256) workgroups of the 128-channel
-// tile against ceil(blocks64 / 256) of half the work each.  A lone workgroup
-// per CU (one wave per SIMD) hides no MFMA latency, so up to 256 workgroups
-// the 64-channel tile is taken.
+// idle or half-loaded; the 64-channel tile doubles the workgroup count at 5 to 12 %
+// more time per MFMA where both fill the GPU (900 to 1,300 workgroups of the 3x3
+// 128 -> 128, 5x5 64 -> 256 and 6x6 256 -> 512 layers, both types).  With every
+// workgroup resident, the busiest CU sets the time: ceil(blocks / 256) workgroups
+// of the 128-channel tile against ceil(blocks64 / 256) of half the work each.  A lone
+// workgroup per CU (one wave per SIMD) hides no MFMA latency, so up to 256
+// workgroups the 64-channel tile is taken (binary32 6x6 layer, 100 workgroups: 225
+// against 373 us; 3x3, 256: 65.8 against 70.0).  Over 50 to 512 workgroups of those
+// layers the rule takes the faster tile or one within 5 %; from 513 to about 640,
+// where the second round of the 128-channel tile is nearly empty, the 64-channel
+// one would be 4 to 9 % faster, from 650 on the 128-channel one is.
 PlanConv mfma_launch_variant(const PlanConv& pc, int F, int Hin, int Win, int dil_h, int dil_w, int pad_h,
                              int pad_w) {
     if (pc.impl == CONV_DIRECT || pc.bn != 128) return pc;
