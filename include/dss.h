@@ -61,7 +61,8 @@ typedef enum dss_status {
 } dss_status;
 
 typedef enum dss_dtype {
-    DSS_F32 = 0,            /* IEEE binary32 */
+    DSS_F32 = 0,            /* IEEE binary32; large contractions run on 16-bit matrix instructions over
+                               several parts per operand, with binary32's precision in every sum */
     DSS_BF16 = 1            /* bfloat16: storage type; arithmetic accumulates in binary32 */
 } dss_dtype;
 
