@@ -149,13 +149,14 @@ __device__ __forceinline__ void split_f16(const float (&v)[8], float scale, u32x
     lo = __builtin_bit_cast(u32x4, l);
 }
 
-// What the parts leave out of the values that may lose bits, in the same unit.
+// What the parts leave out of the values that may lose bits, in the same unit (a bound
+// for the smallest, whose product with the scale may underflow): 0 or 2^-83 and more.
 __device__ __forceinline__ float split_loss(const float (&v)[8], float scale) {
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float y = v[i] * scale, r = y - (float)(_Float16)y;
-        sum += fabsf(y) < 0.25f ? fabsf(r - (float)(_Float16)r) : 0.f;
+        sum += fabsf(y) >= 0.25f || v[i] == 0.f ? 0.f : fabsf(y) < 0x1p-60f ? 0x1p-60f : fabsf(r - (float)(_Float16)r);
     }
     return sum;
 }
@@ -501,14 +502,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     char* dst = halo0 + (p0 + 64 * r) * PITCH + st_q * 16;
                     *reinterpret_cast<u32x4*>(dst) = hi;
                     *reinterpret_cast<u32x4*>(dst + 64) = lo;
+                    const uint32_t x = mb ? un : 0u;          // (a sample of zeros loses nothing)
                     if (st_q == 0) {
                         *reinterpret_cast<uint32_t*>(dst + kScaleAt) = un;
-                        const uint32_t x = mb ? un : 0u;      // (a sample of zeros loses nothing)
                         uint32_t* const rec = reinterpret_cast<uint32_t*>(dst + kLossAt);
                         if (cn == 0) *reinterpret_cast<uint2*>(rec) = make_uint2(0u, x);
                         else atomicMax(rec + 1, x);
                     }
-                    un_max = max(un_max, un);
+                    un_max = max(un_max, x);
                     // a value other than 0 below 2^-2 / S may lose bits (twice its magnitude less 1: 0 comes last)
                     uint32_t mn = ~0u;
 #pragma unroll
@@ -520,7 +521,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     for (int r = 0; r < kRounds; ++r) {
                         if (p0 + 64 * r >= halo_px) break;
                         const uint32_t mb = top_bits(v[r]), sb = scale_bits(mb);
-                        float lost = split_loss(v[r], __uint_as_float(sb)) * __uint_as_float(kUnscale - sb);
+                        float lost = split_loss(v[r], __uint_as_float(sb));
+                        if (lost > 0.f) lost = fmaxf(lost * __uint_as_float(kUnscale - sb), 0x1p-149f);
                         if (mb < (31u << 23) && mb != 0) lost = __builtin_inff();   // S could not follow
                         lost += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(lost), 0xB1, 0xf, 0xf, true));
                         lost += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(lost), 0x4E, 0xf, 0xf, true));
@@ -750,9 +752,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     // with the workgroup's L and X for all outputs, then, hardly ever, with the
     // window's own.
     if constexpr (!BF16) {
-        const float kCert = 32768.f * cert;              // 2^15 times the certificate's factor
+        // 2^15 times the certificate's factor, of which 2^28 go to L and X ahead of their products.
+        // (X at least 2^-94: then its product with a filter's loss does not underflow.  Signals
+        // below 2^-65 are summed again somewhat more often for it.)
+        const float kCert = cert * 0x1p-13f;
+        auto largest = [](float x) { return x > 0.f ? fmaxf(x * 0x1p28f, 0x1p-66f) : 0.f; };
         const float* const head = reinterpret_cast<const float*>(lds);
-        const float l_all = 2.f * head[0], x_all = 2.f * head[1];
+        const float l_all = 0x1p29f * head[0], x_all = 2.f * largest(head[1]);
         uint32_t worst = 0;                              // of |sum| - threshold: negative, infinite and NaN come last
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -811,6 +817,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 int here = 0;
                 asm volatile("" : "+s"(here));
                 const float* const sc = w_scale + here;
+                const float xs = largest(x[mt]);
                 // bit nt 4 + v: output v of tile (mt, nt).  (Padded channels have zero weights and no
                 // threshold; an infinity makes them NaN, which a projection would add.)
                 uint32_t bad = 0;
@@ -821,7 +828,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         // (explicit fmas: the same decision in every instantiation)
-                        const float d = fmaf(-kCert * fmaf(x[mt], wl[v], l[mt]), e[v], fabsf(acc[mt][nt][v]));
+                        const float d = fmaf(-kCert * fmaf(xs, wl[v], 0x1p28f * l[mt]), e[v], fabsf(acc[mt][nt][v]));
                         bad |= (uint32_t)(__float_as_uint(d) >= 0x7f800000u) << (nt * 4 + v);
                     }
                 }

@@ -131,8 +131,9 @@ def test_input_gradient_of_different_channels():
 
 
 # one channel 2^r times the others under weights 2^-r; channels in two groups that no filter sees together; a signal of
-# magnitudes 2^-130 .. 2^-90 (subnormal numbers among them) under weights of 2^100; rows of different magnitude
-@pytest.mark.parametrize("data", ["r12", "r16", "r20", "r24", "r30", "r36", "r41", "r60", "groups", "tiny", "mixed"])
+# magnitudes 2^-130 .. 2^-90 (subnormal numbers among them) under weights of 2^100; channels of random magnitude; the
+# two groups 2^170 apart (products with the scale underflow); a silent channel with weights of 2^40 in a signal of 2^-90
+@pytest.mark.parametrize("data", ["r12", "r16", "r20", "r24", "r30", "r36", "r41", "r60", "groups", "tiny", "mixed", "far", "unused"])
 @pytest.mark.parametrize("case", list(CASES))
 def test_input_channels_of_different_magnitude(case, data):
     w, nd = make(case, 84)
@@ -148,6 +149,17 @@ def test_input_channels_of_different_magnitude(case, data):
         w.x[a] *= np.float32(2.0 ** 34)
         for n in range(conv["cout"]):
             conv["weight"][n, a == (n % 2 == 0)] = 0
+    elif data == "far":
+        a = np.arange(conv["cin"]) % 2 == 0
+        w.x[a] *= np.float32(2.0 ** 110)
+        w.x[~a] *= np.float32(2.0 ** -60)
+        for n in range(conv["cout"]):
+            conv["weight"][n, a == (n % 2 == 0)] = 0
+    elif data == "unused":
+        ch = rng.integers(0, conv["cin"])
+        w.x *= np.float32(2.0 ** -90)
+        w.x[ch] = 0
+        conv["weight"][:, ch] *= np.float32(2.0 ** 40)
     elif data == "tiny":
         w.x *= (2.0 ** rng.uniform(-130, -90, size=w.x.shape)).astype(np.float32)
         conv["weight"] *= np.float32(2.0 ** 100)
