@@ -133,7 +133,7 @@ struct WgradPlan {
     int otiles = 0, itiles = 0, splits = 0;
     int64_t positions = 0;       // F * E_h * U_w: output rows read over the input width
     int64_t nchunks = 0, partial_floats = 0;
-    bool split = false;          // on the binary16-part kernel
+    bool split = false;          // on the bfloat16-part kernel
     int64_t bias_partial_floats = 0;   // after the weight partial sums in the same buffer (with the split
                                        // kernel's flags, one word per workgroup)
 };

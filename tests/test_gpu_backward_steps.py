@@ -32,7 +32,7 @@ def test_pool_and_narrow_backward(mid, cout, H, W, act):
         np.testing.assert_array_equal(a.cpu().numpy().astype(np.float64), b)
 
 
-# 20 and 32 input channels: half a tile of the weight gradient's binary16-part kernel, 1 to 7 taps a group
+# 20 and 32 input channels: half a tile of the weight gradient's bfloat16-part kernel, 1 to 7 taps a group
 @pytest.mark.parametrize("cin", [20, 32])
 @pytest.mark.parametrize("fw", [1, 2, 3, 4, 5, 6, 7])
 def test_weight_gradient_half_tile(cin, fw):

@@ -145,8 +145,7 @@ def _weight_gradient(x, G, fh, fw):
 
 
 # taps per group 1..7 (the kernel's instantiations, 8 in two groups of 4), channels past one 64-wide tile, several
-# splits; "rising": magnitudes that grow by 1e8 along the signal after a zero start, so the scales are lowered on the
-# way; "inf" / "nan": one such sample
+# splits; "rising": magnitudes that grow by 1e8 along the signal after a zero start; "inf" / "nan": one such sample
 @pytest.mark.parametrize("fw", [1, 2, 3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("data", ["plain", "rising", "inf", "nan"])
 def test_weight_gradient_parts(fw, data):
